@@ -129,6 +129,17 @@ struct TileArgs {
     double scale;
 };
 
+// Renormalisation hand-off from the pass before: p null, none; count 0, *p is
+// the factor; else the factor is 1 / sqrt of the sum of p[0 .. count).
+struct RenormIn {
+    const double *p;
+    unsigned count;
+};
+// Partials a pass sums itself (every wave reads them all, 2 KB at most: 4 per
+// lane at 256, where the wait hides behind the state's loads).
+static constexpr unsigned kRenormDirect = 256;
+static constexpr unsigned kRenormOneBlock = 16384;
+
 // Arguments of a single-rotation sweep.
 struct PlainArgs {
     uint64_t x, z;
@@ -168,16 +179,17 @@ prx_status plan_create_cfg(const prx_sched *sched, int n, prx_dtype dtype, const
 
 // ------------------------------------------------------------ launchers
 // All enqueue on `stream` and return hipGetLastError() of the launch.
-// `cap` limits the workgroups of a launch (at most kMaxGridBlocks); the
-// kernels stride over the rest.
+// `cap` limits the workgroups of a launch (at most kMaxGridBlocks), `blocks`
+// is their number (span_blocks, tile_launch_blocks); the kernels stride over
+// the rest.
 hipError_t launch_plain(prx_dtype dt, void *psi, const PlainArgs &a, hipStream_t s,
                         unsigned cap);
 hipError_t launch_span(prx_dtype dt, int m, void *psi, const SpanArgs &a, const void *rots,
-                       const double *renorm_in, double *norm_out, hipStream_t s,
-                       unsigned *blocks_out, unsigned cap);
+                       const RenormIn &renorm_in, double *norm_out, hipStream_t s,
+                       unsigned blocks);
 hipError_t launch_tile(prx_dtype dt, int B, int m, void *psi, const TileArgs &a,
-                       const void *rots, const ChunkRec *chunks, const double *renorm_in,
-                       double *norm_out, hipStream_t s, unsigned *blocks_out, unsigned cap);
+                       const void *rots, const ChunkRec *chunks, const RenormIn &renorm_in,
+                       double *norm_out, hipStream_t s, unsigned blocks);
 // Qubit relabelling: one pass over the state, in place (every 2^12-element
 // group is closed under the permutation).
 hipError_t launch_permute(prx_dtype dt, void *psi, const PermArgs &a, hipStream_t s,
@@ -194,6 +206,9 @@ hipError_t launch_renorm_finish(const double *partials, unsigned count, double *
 static constexpr uint64_t kMaxGridBlocks = 1ull << 22;
 unsigned span_blocks(int n, int m, unsigned cap);
 unsigned tile_blocks(int n, int B, unsigned cap);
+// the workgroups of a tile pass's launch: tile_blocks, or for the persistent
+// shapes those resident on the device, if fewer
+unsigned tile_launch_blocks(prx_dtype dt, int B, int m, int n, unsigned cap);
 unsigned plain_blocks(int n, bool diag, unsigned cap);
 bool span_supported(prx_dtype dt, int m);
 bool tile_supported(prx_dtype dt, int B, int m);

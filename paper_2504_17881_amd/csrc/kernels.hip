@@ -112,12 +112,48 @@ __global__ void __launch_bounds__(256) k_plain_diag(Cx<T> *__restrict__ psi, Pla
     }
 }
 
+// ------------------------------------------------- renormalisation hand-off
+
+// Neumaier-compensated accumulator.
+struct Neu {
+    double s = 0.0, c = 0.0;
+    __device__ __forceinline__ void add(double v) {
+        const double t = s + v;
+        if (fabs(s) >= fabs(v))
+            c += (s - t) + v;
+        else
+            c += (v - t) + s;
+        s = t;
+    }
+    __device__ __forceinline__ double value() const { return s + c; }
+};
+
+// The factor 1 / sqrt(norm) a pass takes over from the pass before it: read
+// from one scalar, or, where the earlier pass left at most kRenormDirect
+// partial sums, summed here by every wave (a fixed order, so all waves get
+// the same bits).  The partials come from L2 while the pass's first state
+// loads are in flight; the two reduction launches this replaces took 3.9 us
+// of the 11.5 us of a 17-qubit complex64 pass and 7 of 20 us at 20 qubits.
+__device__ __forceinline__ double renorm_factor(const RenormIn &in) {
+    if (!in.p) return 1.0;
+    if (in.count == 0) return *in.p;
+    Neu acc;
+    for (unsigned i = threadIdx.x & 63u; i < in.count; i += 64u) acc.add(in.p[i]);
+    double v = acc.value();
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m, 64);
+    const uint64_t u = __double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return 1.0 / sqrt(__longlong_as_double(((uint64_t)hi << 32) | lo));
+}
+
 // ------------------------------------------------------------------ span
 
 template <typename T, int M>
 __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs a,
                                               const RotRec<T> *__restrict__ rots,
-                                              const double *__restrict__ renorm_in,
+                                              RenormIn renorm_in,
                                               double *__restrict__ norm_out) {
     __shared__ double red[4];
     const uint64_t ncos = 1ull << (a.n - M);
@@ -125,8 +161,7 @@ __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs 
     X[0] = 0;
 #pragma unroll
     for (int v = 1; v < (1 << M); ++v) X[v] = X[v & (v - 1)] ^ a.basis[__builtin_ctz(v)];
-    double sc = a.scale;
-    if (renorm_in) sc *= *renorm_in;
+    const double sc = a.scale * renorm_factor(renorm_in);
     double F[1 << M];
     pending_factors<M>(F, a.fscale);
     double nrm = 0.0;
@@ -226,7 +261,7 @@ __global__ void __launch_bounds__(1 << (B - M))
     __attribute__((amdgpu_waves_per_eu(TileWaves<T, B, M>::value))) k_tile(Cx<T> *__restrict__ psi, TileArgs a,
                                                       const RotRec<T> *__restrict__ rots,
                                                       const ChunkRec *__restrict__ chunks,
-                                                      const double *__restrict__ renorm_in,
+                                                      RenormIn renorm_in,
                                                       double *__restrict__ norm_out) {
     constexpr int NT = 1 << (B - M);  // threads
     constexpr int PER = 1 << M;       // amplitudes per thread (tile-set 2^B)
@@ -270,9 +305,6 @@ __global__ void __launch_bounds__(1 << (B - M))
     uint32_t tmask[B - M];
     tile_thread_masks<B - M>(tid, tmask);
 
-    double sc = a.scale;
-    if (renorm_in) sc *= *renorm_in;
-    const T s = (T)sc;
     double nrm = 0.0;
 
     // Set order: persistent workgroups stride over the sets; otherwise the
@@ -298,25 +330,19 @@ __global__ void __launch_bounds__(1 << (B - M))
 #pragma unroll
         for (int j = 0; j < GPER; ++j) lds_v[tid + (uint32_t)j * NT] = r[j];
     };
-    if (PERSIST && w < nsets) {
-        load_set(base_of(tile_of(w)));
-        stage_set();
-        __syncthreads();
-    }
+    // (the grid never exceeds the set count, so every workgroup has a first
+    // set; its loads are in flight while the previous pass's partials are
+    // summed)
+    load_set(base_of(tile_of(w)));
+    const T s = (T)(a.scale * renorm_factor(renorm_in));
+    stage_set();
+    __syncthreads();
     for (; w < nsets; w += gridDim.x) {
         const uint64_t tb = tile_of(w);
         const uint64_t base = base_of(tb);
-        if (!PERSIST) {
-            // one set per iteration (several when the grid is capped); a
-            // thread writes only the slots it read in the previous store
-            // epilogue, so no barrier is needed before the staging
-            load_set(base);
-            stage_set();
-            __syncthreads();
-        }
         const uint32_t wn = w + gridDim.x;
-        const bool next = PERSIST && wn < nsets;
-        if (next) load_set(base_of(tile_of(wn)));
+        const bool next = wn < nsets;  // not persistent: only when the grid is capped
+        if (PERSIST && next) load_set(base_of(tile_of(wn)));
 
         tile_chunks<T, B, M>(lds_raw, tmask, tb, chunks + a.chunk_begin, a.chunk_count, rots);
 
@@ -334,6 +360,7 @@ __global__ void __launch_bounds__(1 << (B - M))
             }
         }
         if (next) {
+            if (!PERSIST) load_set(base_of(tile_of(wn)));
             // the staging writes exactly the slots this thread read in the
             // store epilogue above (LDS operations of a wave stay in order),
             // so only the chunk gathers of the next set wait at a barrier
@@ -408,20 +435,6 @@ __global__ void __launch_bounds__(256) k_permute(Cx<T> *__restrict__ psi, PermAr
 }
 
 // ------------------------------------------------------------ reductions
-
-// Neumaier-compensated accumulator.
-struct Neu {
-    double s = 0.0, c = 0.0;
-    __device__ __forceinline__ void add(double v) {
-        const double t = s + v;
-        if (fabs(s) >= fabs(v))
-            c += (s - t) + v;
-        else
-            c += (v - t) + s;
-        s = t;
-    }
-    __device__ __forceinline__ double value() const { return s + c; }
-};
 
 // Fixed-shape tree over the block (deterministic for a fixed launch shape).
 __device__ __forceinline__ double tree256(double v, double *sh) {
@@ -508,14 +521,14 @@ __global__ void __launch_bounds__(256) k_renorm_stage1(const double *__restrict_
     if (threadIdx.x == 0) stage[blockIdx.x] = s;
 }
 
-// Stage 2: sums the stage-1 values and writes 1/sqrt(sum).
-__global__ void __launch_bounds__(256) k_renorm_finish(const double *__restrict__ stage,
-                                                       unsigned count,
-                                                       double *__restrict__ scale_out) {
-    __shared__ double sh[256];
+// Last stage: sums `count` values and writes 1/sqrt(sum).
+__global__ void __launch_bounds__(1024) k_renorm_finish(const double *__restrict__ v,
+                                                        unsigned count,
+                                                        double *__restrict__ scale_out) {
+    __shared__ double red[16];
     Neu acc;
-    for (unsigned i = threadIdx.x; i < count; i += 256u) acc.add(stage[i]);
-    const double s = tree256(acc.value(), sh);
+    for (unsigned i = threadIdx.x; i < count; i += 1024u) acc.add(v[i]);
+    const double s = block_sum<1024>(acc.value(), red);
     if (threadIdx.x == 0) scale_out[0] = 1.0 / sqrt(s);
 }
 
@@ -615,10 +628,7 @@ bool span_supported(prx_dtype, int m) { return m >= 1 && m <= 5; }
 
 template <typename T>
 static hipError_t span_t(int m, void *psi, const SpanArgs &a, const void *rots,
-                         const double *rin, double *nout, hipStream_t s, unsigned *blocks,
-                         unsigned cap) {
-    const unsigned nb = span_blocks(a.n, m, cap);
-    *blocks = nb;
+                         const RenormIn &rin, double *nout, hipStream_t s, unsigned nb) {
     const RotRec<T> *r = (const RotRec<T> *)rots;
     Cx<T> *p = (Cx<T> *)psi;
     switch (m) {
@@ -633,10 +643,10 @@ static hipError_t span_t(int m, void *psi, const SpanArgs &a, const void *rots,
 }
 
 hipError_t launch_span(prx_dtype dt, int m, void *psi, const SpanArgs &a, const void *rots,
-                       const double *renorm_in, double *norm_out, hipStream_t s,
-                       unsigned *blocks_out, unsigned cap) {
-    return dt == PRX_C64 ? span_t<float>(m, psi, a, rots, renorm_in, norm_out, s, blocks_out, cap)
-                         : span_t<double>(m, psi, a, rots, renorm_in, norm_out, s, blocks_out, cap);
+                       const RenormIn &renorm_in, double *norm_out, hipStream_t s,
+                       unsigned blocks) {
+    return dt == PRX_C64 ? span_t<float>(m, psi, a, rots, renorm_in, norm_out, s, blocks)
+                         : span_t<double>(m, psi, a, rots, renorm_in, norm_out, s, blocks);
 }
 
 // (B, M) pairs instantiated for the tile kernel.
@@ -654,48 +664,73 @@ bool tile_supported(prx_dtype dt, int B, int m) {
 }
 
 template <typename T, int B, int M>
+static unsigned tile_blocks_one(int n, unsigned cap) {
+    return TilePersist<T, B>::value
+               ? tile_grid((const void *)k_tile<T, B, M>, n, B, 1 << (B - M), cap)
+               : tile_blocks(n, B, cap);
+}
+
+template <typename T, int B, int M>
 static hipError_t tile_launch_one(void *psi, const TileArgs &a, const void *rots,
-                                  const ChunkRec *chunks, const double *rin, double *nout,
-                                  hipStream_t s, unsigned *blocks, unsigned cap) {
-    const unsigned nb = TilePersist<T, B>::value
-                            ? tile_grid((const void *)k_tile<T, B, M>, a.n, B, 1 << (B - M), cap)
-                            : tile_blocks(a.n, B, cap);
-    *blocks = nb;
+                                  const ChunkRec *chunks, const RenormIn &rin, double *nout,
+                                  hipStream_t s, unsigned nb) {
     hipLaunchKernelGGL((k_tile<T, B, M>), dim3(nb), dim3(1 << (B - M)), 0, s, (Cx<T> *)psi, a,
                        (const RotRec<T> *)rots, chunks, rin, nout);
     return hipGetLastError();
 }
 
+// Expands X(T, B, M) for the built shape (T, B, m).
+#define PRX_TILE_CASE(BB, MM)                                                  \
+    if (B == BB && m == MM) {                                                  \
+        if constexpr (sizeof(T) == 4 || BB <= 12 || (BB == 13 && MM == 4)) {   \
+            PRX_TILE_BODY(BB, MM)                                              \
+        }                                                                      \
+    }
+
 template <typename T>
 static hipError_t tile_t(int B, int m, void *psi, const TileArgs &a, const void *rots,
-                         const ChunkRec *chunks, const double *rin, double *nout, hipStream_t s,
-                         unsigned *blocks, unsigned cap) {
-#define PRX_TL(BB, MM)                                                                         \
-    if (B == BB && m == MM) {                                                                  \
-        if constexpr (sizeof(T) == 4 || BB <= 12 || (BB == 13 && MM == 4))                    \
-            return tile_launch_one<T, BB, MM>(psi, a, rots, chunks, rin, nout, s, blocks, cap); \
-        return hipErrorInvalidValue;                                                      \
-    }
-    PRX_TILE_SHAPES(PRX_TL)
-#undef PRX_TL
+                         const ChunkRec *chunks, const RenormIn &rin, double *nout, hipStream_t s,
+                         unsigned nb) {
+#define PRX_TILE_BODY(BB, MM) return tile_launch_one<T, BB, MM>(psi, a, rots, chunks, rin, nout, s, nb);
+    PRX_TILE_SHAPES(PRX_TILE_CASE)
+#undef PRX_TILE_BODY
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_tile(prx_dtype dt, int B, int m, void *psi, const TileArgs &a,
-                       const void *rots, const ChunkRec *chunks, const double *renorm_in,
-                       double *norm_out, hipStream_t s, unsigned *blocks_out, unsigned cap) {
-    return dt == PRX_C64
-               ? tile_t<float>(B, m, psi, a, rots, chunks, renorm_in, norm_out, s, blocks_out, cap)
-               : tile_t<double>(B, m, psi, a, rots, chunks, renorm_in, norm_out, s, blocks_out, cap);
+template <typename T>
+static unsigned tile_launch_blocks_t(int B, int m, int n, unsigned cap) {
+#define PRX_TILE_BODY(BB, MM) return tile_blocks_one<T, BB, MM>(n, cap);
+    PRX_TILE_SHAPES(PRX_TILE_CASE)
+#undef PRX_TILE_BODY
+    return tile_blocks(n, B, cap);
 }
 
+unsigned tile_launch_blocks(prx_dtype dt, int B, int m, int n, unsigned cap) {
+    return dt == PRX_C64 ? tile_launch_blocks_t<float>(B, m, n, cap)
+                         : tile_launch_blocks_t<double>(B, m, n, cap);
+}
+
+hipError_t launch_tile(prx_dtype dt, int B, int m, void *psi, const TileArgs &a,
+                       const void *rots, const ChunkRec *chunks, const RenormIn &renorm_in,
+                       double *norm_out, hipStream_t s, unsigned blocks) {
+    return dt == PRX_C64
+               ? tile_t<float>(B, m, psi, a, rots, chunks, renorm_in, norm_out, s, blocks)
+               : tile_t<double>(B, m, psi, a, rots, chunks, renorm_in, norm_out, s, blocks);
+}
+
+// A hand-off too long for the next pass to sum itself: one workgroup up to
+// kRenormOneBlock partials (a 24-qubit pass of 4096), two launches beyond.
 hipError_t launch_renorm_finish(const double *partials, unsigned count, double *scale_out,
                                 hipStream_t s) {
     // scale_out[1 .. kRenormStage] holds the stage-1 sums
     double *stage = scale_out + 1;
-    const unsigned g = count < 4096u ? 1u : kRenormStage;
-    hipLaunchKernelGGL(k_renorm_stage1, dim3(g), dim3(256), 0, s, partials, count, stage);
-    hipLaunchKernelGGL(k_renorm_finish, dim3(1), dim3(256), 0, s, stage, g, scale_out);
+    if (count > kRenormOneBlock) {
+        hipLaunchKernelGGL(k_renorm_stage1, dim3(kRenormStage), dim3(256), 0, s, partials, count,
+                           stage);
+        partials = stage;
+        count = kRenormStage;
+    }
+    hipLaunchKernelGGL(k_renorm_finish, dim3(1), dim3(1024), 0, s, partials, count, scale_out);
     return hipGetLastError();
 }
 

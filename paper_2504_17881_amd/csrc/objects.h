@@ -80,7 +80,11 @@ void tile_args(int n, const Pass &ps, TileArgs &a);
 struct WsLayout {
     size_t rot_off = 0, rot_bytes = 0;
     size_t chunk_off = 0, chunk_bytes = 0;
+    // norm partials; a hand-off of at most `direct` partials is summed by the
+    // next pass itself, which meanwhile writes its own at the other of two
+    // places, [0, direct) and [direct, 2 direct)
     size_t part_off = 0, part_bytes = 0;
+    unsigned direct = 0;
     size_t scal_off = 0, scal_bytes = 0;
     size_t total = 0;
 };

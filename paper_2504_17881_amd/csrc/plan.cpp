@@ -930,10 +930,19 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         w.chunk_off = align256(w.rot_off + w.rot_bytes + kRecordReadAhead);
         w.chunk_bytes = P->chunks.size() * sizeof(ChunkRec);
         w.part_off = align256(w.chunk_off + w.chunk_bytes);
-        w.part_bytes = maxblocks * sizeof(double);
-        w.scal_off = align256(w.part_off + w.part_bytes);
         w.scal_bytes = (1 + kRenormStage) * sizeof(double);
-        w.total = align256(w.scal_off + w.scal_bytes);
+        w.direct = (unsigned)std::min<size_t>(maxblocks, kRenormDirect);
+        auto place = [&](size_t parts) {
+            w.part_bytes = parts * sizeof(double);
+            w.scal_off = align256(w.part_off + w.part_bytes);
+            w.total = align256(w.scal_off + w.scal_bytes);
+        };
+        place(std::max<size_t>(maxblocks, 2 * w.direct));
+        if (w.total > PRX_STATIC_WS_BYTES) {
+            // a plan at the edge of the static buffer keeps the one region
+            w.direct = 0;
+            place(maxblocks);
+        }
     } catch (const std::bad_alloc &) {
         delete P;
         return fail(PRX_ERR_OOM, "out of host memory");
@@ -1020,11 +1029,23 @@ static prx_status execute_impl(const prx_plan *P, void *psi, void *ws, size_t ws
     const ChunkRec *chunks = (const ChunkRec *)(base + P->ws.chunk_off);
     double *part = (double *)(base + P->ws.part_off);
     double *scal = (double *)(base + P->ws.scal_off);
+    auto blocks_of = [&](const Pass &ps) -> unsigned {
+        if (ps.kind == kSpan) return span_blocks(P->n, ps.m, P->cfg.grid_cap);
+        if (ps.kind == kTile)
+            return tile_launch_blocks(P->dtype, ps.B, ps.m, P->n, P->cfg.grid_cap);
+        return 0;
+    };
+    RenormIn handed{nullptr, 0};  // what the previous pass left
+    unsigned next_blocks = P->passes.empty() ? 0 : blocks_of(P->passes[0]);
     for (size_t i = 0; i < P->passes.size(); ++i) {
         const Pass &ps = P->passes[i];
-        const double *rin = ps.renorm_in ? scal : nullptr;
+        const unsigned blocks = next_blocks;
+        next_blocks = i + 1 < P->passes.size() ? blocks_of(P->passes[i + 1]) : 0;
+        const RenormIn rin = ps.renorm_in ? handed : RenormIn{nullptr, 0};
         double *nout = ps.norm_out ? part : nullptr;
-        unsigned blocks = 0;
+        // summing in the next pass needs both passes' partials in place: this
+        // pass's may not overwrite what it reads, nor the next one's these
+        if (nout && rin.count && rin.p == part) nout = part + P->ws.direct;
         hipError_t e = hipSuccess;
         if (ev) PRX_HIP(hipEventRecord(ev[3 * i], s));
         if (ps.kind == kPlain) {
@@ -1058,18 +1079,23 @@ static prx_status execute_impl(const prx_plan *P, void *psi, void *ws, size_t ws
             a.n = P->n;
             a.scale = ps.scale;
             for (int k = 0; k < kMaxChunkRank; ++k) a.fscale[k] = ps.fscale[k];
-            e = launch_span(P->dtype, ps.m, psi, a, rots, rin, nout, s, &blocks, P->cfg.grid_cap);
+            e = launch_span(P->dtype, ps.m, psi, a, rots, rin, nout, s, blocks);
         } else {
             TileArgs a;
             tile_args(P->n, ps, a);
-            e = launch_tile(P->dtype, ps.B, ps.m, psi, a, rots, chunks, rin, nout, s, &blocks,
-                            P->cfg.grid_cap);
+            e = launch_tile(P->dtype, ps.B, ps.m, psi, a, rots, chunks, rin, nout, s, blocks);
         }
         if (e != hipSuccess) return hip_fail(e, "pass launch");
         if (ev) PRX_HIP(hipEventRecord(ev[3 * i + 1], s));
         if (ps.norm_out) {
-            e = launch_renorm_finish(part, blocks, scal, s);
-            if (e != hipSuccess) return hip_fail(e, "renorm launch");
+            const Pass &nx = P->passes[i + 1];
+            if (blocks <= P->ws.direct && (!nx.norm_out || next_blocks <= P->ws.direct)) {
+                handed = RenormIn{nout, blocks};
+            } else {
+                e = launch_renorm_finish(nout, blocks, scal, s);
+                if (e != hipSuccess) return hip_fail(e, "renorm launch");
+                handed = RenormIn{scal, 0};
+            }
         }
         if (ev) PRX_HIP(hipEventRecord(ev[3 * i + 2], s));
     }
