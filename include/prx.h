@@ -145,7 +145,8 @@ void prx_sched_destroy(prx_sched *s);
 
 /* Optional planner settings; zero fields take defaults. */
 typedef struct {
-    int tile_qubits;     /* qubits held by one workgroup in the tile kernel (default per dtype) */
+    int tile_qubits;     /* qubits held by one workgroup in the tile kernel (default per dtype
+                            and n) */
     int chunk_rank;      /* rotations' X-span rank a thread holds in registers (default 4) */
     int max_fuse;        /* max rotations per tile pass (default 128) */
     int span_max;        /* max rotations per span pass (default: chunk_rank and repeats) */
@@ -210,6 +211,12 @@ prx_status prx_plan_execute_timed(const prx_plan *plan, void *psi, void *ws, siz
                                   void *stream, float *pass_ms, float *renorm_ms);
 
 /* Plan inspection (read-only views for tests and tools).
+ *
+ * A fused plan of 4 to 14 qubits (13 for PRX_C128) that names no tile or span
+ * option is resident where that is the faster form: every pass is a tile pass
+ * of the whole state (B = b = n, g = 0), and prx_plan_execute runs all of
+ * them in one launch with the state in one workgroup's LDS
+ * (prx_plan_execute_timed launches them one by one).
  *
  * Passes: kind 0 = single-rotation sweep, 1 = span pass (one chunk in the
  * global index frame, `basis`/`pivot` valid), 2 = tile pass (workgroup

@@ -162,7 +162,7 @@ struct BTSample {
 struct BatchTileArgs {
     const BTSample *samples;
     const TileArgs *passes;
-    const ChunkRec *chunks;
+    const void *chunks;
     const void *rots;
     const uint64_t *prefixW;  // S_t + 1 tile-set counts over the sorted samples
     const uint32_t *order;
@@ -171,7 +171,7 @@ struct BatchTileArgs {
 template <typename T, int B, int M>
 __global__ void __launch_bounds__(1 << (B - M))
     k_batch_tile_round(const BTSample *__restrict__ samples, const TileArgs *__restrict__ passes,
-                       const ChunkRec *__restrict__ chunks, const void *__restrict__ rot_table,
+                       const ChunkRec<T> *__restrict__ chunks, const void *__restrict__ rot_table,
                        const uint64_t *__restrict__ prefixW, const uint32_t *__restrict__ order,
                        uint32_t p, uint32_t active, uint64_t items) {
     constexpr int NT = 1 << (B - M);
@@ -257,7 +257,7 @@ struct prx_batch {
     std::vector<prx::BTSample> tsamples;
     std::vector<uint32_t> tsrc;  // tile-mode sample -> sample
     std::vector<prx::TileArgs> tpasses;
-    std::vector<prx::ChunkRec> tchunks;
+    std::vector<unsigned char> tchunks;  // ChunkRec<float> or ChunkRec<double> image
     std::vector<uint64_t> tprefix;
     std::vector<uint32_t> torder;
     std::vector<uint32_t> tround_active;
@@ -298,6 +298,7 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
         b->S = S;
         b->dtype = dtype;
         const size_t rsz = dtype == PRX_C64 ? sizeof(RotRec<float>) : sizeof(RotRec<double>);
+        const size_t csz = dtype == PRX_C64 ? sizeof(ChunkRec<float>) : sizeof(ChunkRec<double>);
         const int TB = batch_tile_qubits(dtype);
         PlanCfg span_cfg;
         span_cfg.span_only = true;
@@ -341,7 +342,7 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
                 ts.nsets = (uint32_t)(1ull << (n[s] - TB));
                 ts.pass_begin = (uint32_t)b->tpasses.size();
                 ts.pass_count = (uint32_t)P->passes.size();
-                const uint32_t chunk_base = (uint32_t)b->tchunks.size();
+                const uint32_t chunk_base = (uint32_t)(b->tchunks.size() / csz);
                 for (const Pass &ps : P->passes) {
                     if (ps.kind != kTile || ps.B != TB || ps.m != kBatchTileM) {
                         prx_plan_destroy(P);
@@ -353,10 +354,10 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
                     ta.chunk_begin += chunk_base;
                     b->tpasses.push_back(ta);
                 }
-                for (ChunkRec ch : P->chunks) {
-                    ch.rot_begin += rot_base;
-                    b->tchunks.push_back(ch);
-                }
+                const size_t at = b->tchunks.size();
+                b->tchunks.insert(b->tchunks.end(), P->chunk_table.begin(), P->chunk_table.end());
+                for (size_t c = at; c < b->tchunks.size(); c += csz)
+                    reinterpret_cast<ChunkHead *>(b->tchunks.data() + c)->rot_begin += rot_base;
                 b->tsamples.push_back(ts);
             } else {
                 sm.pass_count = (uint32_t)P->passes.size();
@@ -421,7 +422,7 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
         b->off_order = o;    o = al256(o + S * sizeof(uint32_t));
         b->off_tsamples = o; o = al256(o + St * sizeof(BTSample));
         b->off_tpasses = o;  o = al256(o + b->tpasses.size() * sizeof(TileArgs));
-        b->off_tchunks = o;  o = al256(o + b->tchunks.size() * sizeof(ChunkRec));
+        b->off_tchunks = o;  o = al256(o + b->tchunks.size());
         b->off_tprefix = o;  o = al256(o + b->tprefix.size() * sizeof(uint64_t));
         b->off_torder = o;   o = al256(o + St * sizeof(uint32_t));
         b->total = o;
@@ -484,8 +485,7 @@ prx_status prx_batch_upload(prx_batch *b, void *const *psi, void *ws, size_t ws_
                                b->tpasses.size() * sizeof(TileArgs), hipMemcpyHostToDevice, st));
         if (!b->tchunks.empty())
             PRX_HIP(hipMemcpyAsync(w + b->off_tchunks, b->tchunks.data(),
-                                   b->tchunks.size() * sizeof(ChunkRec), hipMemcpyHostToDevice,
-                                   st));
+                                   b->tchunks.size(), hipMemcpyHostToDevice, st));
         PRX_HIP(hipMemcpyAsync(w + b->off_tprefix, b->tprefix.data(),
                                b->tprefix.size() * sizeof(uint64_t), hipMemcpyHostToDevice, st));
         PRX_HIP(hipMemcpyAsync(w + b->off_torder, b->torder.data(), St * sizeof(uint32_t),
@@ -510,7 +510,7 @@ prx_status prx_batch_execute(const prx_batch *b, void *ws, size_t ws_bytes,
     BatchTileArgs ta;
     ta.samples = (const BTSample *)(w + b->off_tsamples);
     ta.passes = (const TileArgs *)(w + b->off_tpasses);
-    ta.chunks = (const ChunkRec *)(w + b->off_tchunks);
+    ta.chunks = w + b->off_tchunks;
     ta.rots = w + b->off_rots;
     ta.prefixW = (const uint64_t *)(w + b->off_tprefix);
     ta.order = (const uint32_t *)(w + b->off_torder);
@@ -531,11 +531,13 @@ prx_status prx_batch_execute(const prx_batch *b, void *ws, size_t ws_bytes,
             const unsigned grid = (unsigned)std::min<uint64_t>(titems, tcap);
             if (b->dtype == PRX_C64)
                 hipLaunchKernelGGL((k_batch_tile_round<float, 12, kBatchTileM>), dim3(grid),
-                                   dim3(tile_threads), 0, st, ta.samples, ta.passes, ta.chunks,
-                                   ta.rots, ta.prefixW, ta.order, p, tactive, titems);
+                                   dim3(tile_threads), 0, st, ta.samples, ta.passes,
+                                   (const ChunkRec<float> *)ta.chunks, ta.rots, ta.prefixW,
+                                   ta.order, p, tactive, titems);
             else
                 hipLaunchKernelGGL((k_batch_tile_round<double, 11, kBatchTileM>), dim3(grid),
-                                   dim3(tile_threads), 0, st, ta.samples, ta.passes, ta.chunks,
+                                   dim3(tile_threads), 0, st, ta.samples, ta.passes,
+                                   (const ChunkRec<double> *)ta.chunks,
                                    ta.rots, ta.prefixW, ta.order, p, tactive, titems);
             PRX_HIP(hipGetLastError());
         }

@@ -490,12 +490,15 @@ __device__ __forceinline__ void tile_thread_masks(uint32_t tid, uint32_t (&tmask
 
 template <typename T, int B, int M>
 __device__ __forceinline__ void tile_chunks(unsigned char *lds_raw, const uint32_t (&tmask)[B - M],
-                                            uint64_t tb, const ChunkRec *__restrict__ chunks,
+                                            uint64_t tb, const ChunkRec<T> *__restrict__ chunks,
                                             uint32_t count, const RotRec<T> *__restrict__ rots) {
     // LDS byte offsets: the XOR of indices commutes with the element shift
     constexpr uint32_t SH = sizeof(Cx<T>) == 8 ? 3u : 4u;
     for (uint32_t c = 0; c < count; ++c) {
-        const ChunkRec ch = chunks[c];
+        // (the factors too are read here: behind the rotations their load's
+        // latency would add to every chunk, 5 % of a 14-qubit complex128 pass)
+        const ChunkRec<T> rec = chunks[c];
+        const ChunkHead &ch = rec.h;
         uint32_t k0 = 0;
 #pragma unroll
         for (int i = 0; i < B - M; ++i) k0 = xor_and(k0, tmask[i], (uint32_t)ch.cvec[i]);
@@ -512,11 +515,7 @@ __device__ __forceinline__ void tile_chunks(unsigned char *lds_raw, const uint32
         apply_rots<T, M>(amp, k0, tb, rots + ch.rot_begin, ch.rot_count);
 #pragma unroll
         for (int v = 0; v < (1 << M); ++v) {
-            T f;
-            if constexpr (sizeof(T) == 4)
-                f = ch.facf[v];
-            else
-                f = ch.facd[v];
+            const T f = rec.fac[v];
             Cx<T> o;
             o.re = amp[v].re * f;
             o.im = amp[v].im * f;

@@ -88,17 +88,28 @@ static constexpr int kMaxTileThreadBits = 10;
 // k0(t) = XOR of cvec[i] over the bits i set in t; the cvec span a
 // complement of the basis span, and the first ones have independent low
 // bits so that the lanes of one LDS access cycle use distinct banks.
-struct ChunkRec {
+struct ChunkHead {
     uint32_t rot_begin;
     uint32_t rot_count;
+    uint32_t flags;  // resident plans: kChunk* bits
     uint32_t basis[kMaxChunkRank];
     uint16_t cvec[kMaxTileThreadBits];
-    double fscale[kMaxChunkRank];  // pending per-slot factors K at the chunk's end
-    // element v's factor, the product of fscale over the bits set in v
-    // (v < 2^m, m <= 5), in each state precision
-    float facf[32];
-    double facd[32];
+    double scale;    // resident plans, at a pass's last chunk: the pass's scale
 };
+// The device record, in cache lines: the head, then the factors of the coset
+// labels in the state's precision (label v's pending factor, the product of
+// the chunk's per-slot factors K over the bits set in v; v < 2^m, m <= 5).  A
+// rank-4 complex64 chunk reads two lines.
+template <typename T>
+struct ChunkRec {
+    ChunkHead h;
+    T fac[32];
+};
+static_assert(sizeof(ChunkHead) == 64 && sizeof(ChunkRec<float>) == 192 &&
+              sizeof(ChunkRec<double>) == 320, "whole cache lines");
+static constexpr uint32_t kChunkPassEnd = 1;   // last chunk of a pass: its scale applies here,
+static constexpr uint32_t kChunkRenormIn = 2;  // times the renormalisation factor in force;
+static constexpr uint32_t kChunkNormOut = 4;   // and the norm after it makes the next factor
 
 // Longest run of rotations in one chunk (bounds the pending factors: with
 // tau^2 <= 1/2 each kappa lies in [1/2, 3/2]).
@@ -188,8 +199,18 @@ hipError_t launch_span(prx_dtype dt, int m, void *psi, const SpanArgs &a, const 
                        const RenormIn &renorm_in, double *norm_out, hipStream_t s,
                        unsigned blocks);
 hipError_t launch_tile(prx_dtype dt, int B, int m, void *psi, const TileArgs &a,
-                       const void *rots, const ChunkRec *chunks, const RenormIn &renorm_in,
+                       const void *rots, const void *chunks, const RenormIn &renorm_in,
                        double *norm_out, hipStream_t s, unsigned blocks);
+// Resident plans: a state of up to resident_max_qubits(dt) qubits stays in one
+// workgroup's LDS for chunks [chunk_begin, +chunk_count), whatever passes they
+// belong to.  rin (nullable): the renormalisation factor on entry; rout
+// (nullable) receives the one on exit.
+static constexpr int kResidentMinQubits = 4;
+static constexpr int resident_max_qubits(prx_dtype dt) { return dt == PRX_C64 ? 14 : 13; }
+hipError_t launch_resident(prx_dtype dt, void *psi, int n, const void *rots, const void *chunks,
+                           uint32_t chunk_begin, uint32_t chunk_count, const double *rin,
+                           double *rout, hipStream_t s);
+unsigned resident_threads(int n);
 // Qubit relabelling: one pass over the state, in place (every 2^12-element
 // group is closed under the permutation).
 hipError_t launch_permute(prx_dtype dt, void *psi, const PermArgs &a, hipStream_t s,

@@ -260,7 +260,7 @@ template <typename T, int B, int M>
 __global__ void __launch_bounds__(1 << (B - M))
     __attribute__((amdgpu_waves_per_eu(TileWaves<T, B, M>::value))) k_tile(Cx<T> *__restrict__ psi, TileArgs a,
                                                       const RotRec<T> *__restrict__ rots,
-                                                      const ChunkRec *__restrict__ chunks,
+                                                      const ChunkRec<T> *__restrict__ chunks,
                                                       RenormIn renorm_in,
                                                       double *__restrict__ norm_out) {
     constexpr int NT = 1 << (B - M);  // threads
@@ -373,6 +373,131 @@ __global__ void __launch_bounds__(1 << (B - M))
         nrm = block_sum<NT>(nrm, reinterpret_cast<double *>(lds_raw));
         if (tid == 0) norm_out[blockIdx.x] = nrm;
     }
+}
+
+// -------------------------------------------------------------- resident
+
+// A state that fits one workgroup's LDS (14 qubits at complex64, 13 at
+// complex128) stays there for a whole plan: one launch instead of one per
+// pass.  The frame is the global index, so every rotation fits it and a chunk
+// ends only when its basis is full.  Bound by the latency of a chunk's chain
+// (gather, rotations, scatter, barrier) up to 12 qubits, where a SIMD holds
+// one wave, and by one CU's vector ALU and LDS at 14.
+template <typename T, int B>
+struct ResidentShape {
+    static constexpr int M = 4;
+    static constexpr int NT = B > 10 ? 1 << (B - M) : 64;
+};
+
+// Runs chunks [0, count) on the state at psi (n <= B qubits).  The workgroup
+// has NT threads; states of fewer qubits leave whole waves idle (they only
+// wait at the barriers), and below 10 qubits the lanes past the 2^(n-4)
+// cosets repeat them (their complement vectors are zero): a wave's loads
+// precede its stores, and the repeated stores carry equal values.
+template <typename T, int B>
+__device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T> *psi, int n,
+                                             const ChunkRec<T> *__restrict__ chunks,
+                                             uint32_t count, const RotRec<T> *__restrict__ rots,
+                                             const double *rin, double *rout) {
+    typedef ResidentShape<T, B> S;
+    constexpr int M = S::M, NT = S::NT, PER = 1 << M;
+    constexpr uint32_t SH = sizeof(Cx<T>) == 8 ? 3u : 4u;
+    constexpr int G = Group<T>::G;
+    constexpr int GPER = (1 << B) / (G * NT);
+    typedef typename Group<T>::V V;
+    V *lds_v = reinterpret_cast<V *>(lds);
+    unsigned char *lds_raw = reinterpret_cast<unsigned char *>(lds);
+    const uint32_t tid = threadIdx.x;
+    const uint32_t ncos = 1u << (n - M);       // cosets: threads with work
+    const uint32_t ngroups = (1u << n) / G;
+    const uint32_t waves = ncos > 64u ? ncos >> 6 : 1u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    {
+        const V *src = reinterpret_cast<const V *>(psi);
+        V r[GPER];
+#pragma unroll
+        for (int j = 0; j < GPER; ++j)
+            if (tid + (uint32_t)j * NT < ngroups) r[j] = src[tid + (uint32_t)j * NT];
+#pragma unroll
+        for (int j = 0; j < GPER; ++j)
+            if (tid + (uint32_t)j * NT < ngroups) lds_v[tid + (uint32_t)j * NT] = r[j];
+    }
+    double rn = rin ? *rin : 1.0;
+    uint32_t tmask[B - M];
+    tile_thread_masks<B - M>(tid, tmask);
+    uint32_t par = 0;
+    __syncthreads();
+    for (uint32_t c = 0; c < count; ++c) {
+        const ChunkRec<T> rec = chunks[c];
+        const ChunkHead &ch = rec.h;
+        if (wave < waves) {
+            uint32_t k0 = 0;
+#pragma unroll
+            for (int i = 0; i < B - M; ++i) k0 = xor_and(k0, tmask[i], (uint32_t)ch.cvec[i]);
+            const uint32_t k0b = k0 << SH;
+            uint32_t Xb[PER];
+            Xb[0] = 0;
+#pragma unroll
+            for (int v = 1; v < PER; ++v)
+                Xb[v] = Xb[v & (v - 1)] ^ (ch.basis[__builtin_ctz(v)] << SH);
+            Cx<T> amp[PER];
+#pragma unroll
+            for (int v = 0; v < PER; ++v)
+                amp[v] = *reinterpret_cast<const Cx<T> *>(lds_raw + (k0b ^ Xb[v]));
+            apply_rots<T, M>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
+            const double sc = !(ch.flags & kChunkPassEnd) ? 1.0
+                              : ch.flags & kChunkRenormIn ? ch.scale * rn : ch.scale;
+            const T s = (T)sc;
+            double nrm = 0.0;
+#pragma unroll
+            for (int v = 0; v < PER; ++v) {
+                const T f = rec.fac[v];
+                Cx<T> o;
+                o.re = amp[v].re * f;
+                o.im = amp[v].im * f;
+                if (ch.flags & kChunkPassEnd) {
+                    o.re *= s;
+                    o.im *= s;
+                    nrm = fma((double)o.re, (double)o.re, nrm);
+                    nrm = fma((double)o.im, (double)o.im, nrm);
+                }
+                *reinterpret_cast<Cx<T> *>(lds_raw + (k0b ^ Xb[v])) = o;
+            }
+            if (ch.flags & kChunkNormOut) {
+                if (tid >= ncos) nrm = 0.0;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
+                if ((tid & 63u) == 0) red[par][wave] = nrm;
+            }
+        }
+        __syncthreads();
+        if (ch.flags & kChunkNormOut) {
+            // the two places alternate: the next norm may be written before
+            // every wave has read this one
+            double sum = 0.0;
+            for (uint32_t i = 0; i < waves; ++i) sum += red[par][i];
+            rn = 1.0 / sqrt(sum);
+            par ^= 1u;
+        }
+    }
+    {
+        V *dst = reinterpret_cast<V *>(psi);
+#pragma unroll
+        for (int j = 0; j < GPER; ++j)
+            if (tid + (uint32_t)j * NT < ngroups)
+                dst[tid + (uint32_t)j * NT] = lds_v[tid + (uint32_t)j * NT];
+    }
+    if (rout && tid == 0) *rout = rn;
+}
+
+template <typename T, int B>
+__global__ void __launch_bounds__((ResidentShape<T, B>::NT))
+    k_resident(Cx<T> *__restrict__ psi, int n, const ChunkRec<T> *__restrict__ chunks,
+               uint32_t count, const RotRec<T> *__restrict__ rots, const double *rin,
+               double *rout) {
+    __shared__ __align__(16) Cx<T> lds[1 << B];
+    __shared__ double red[2][16];
+    resident_run<T, B>(lds, red, psi, n, chunks, count, rots, rin, rout);
 }
 
 // ------------------------------------------------------------ relabelling
@@ -672,10 +797,10 @@ static unsigned tile_blocks_one(int n, unsigned cap) {
 
 template <typename T, int B, int M>
 static hipError_t tile_launch_one(void *psi, const TileArgs &a, const void *rots,
-                                  const ChunkRec *chunks, const RenormIn &rin, double *nout,
+                                  const void *chunks, const RenormIn &rin, double *nout,
                                   hipStream_t s, unsigned nb) {
     hipLaunchKernelGGL((k_tile<T, B, M>), dim3(nb), dim3(1 << (B - M)), 0, s, (Cx<T> *)psi, a,
-                       (const RotRec<T> *)rots, chunks, rin, nout);
+                       (const RotRec<T> *)rots, (const ChunkRec<T> *)chunks, rin, nout);
     return hipGetLastError();
 }
 
@@ -689,7 +814,7 @@ static hipError_t tile_launch_one(void *psi, const TileArgs &a, const void *rots
 
 template <typename T>
 static hipError_t tile_t(int B, int m, void *psi, const TileArgs &a, const void *rots,
-                         const ChunkRec *chunks, const RenormIn &rin, double *nout, hipStream_t s,
+                         const void *chunks, const RenormIn &rin, double *nout, hipStream_t s,
                          unsigned nb) {
 #define PRX_TILE_BODY(BB, MM) return tile_launch_one<T, BB, MM>(psi, a, rots, chunks, rin, nout, s, nb);
     PRX_TILE_SHAPES(PRX_TILE_CASE)
@@ -711,7 +836,7 @@ unsigned tile_launch_blocks(prx_dtype dt, int B, int m, int n, unsigned cap) {
 }
 
 hipError_t launch_tile(prx_dtype dt, int B, int m, void *psi, const TileArgs &a,
-                       const void *rots, const ChunkRec *chunks, const RenormIn &renorm_in,
+                       const void *rots, const void *chunks, const RenormIn &renorm_in,
                        double *norm_out, hipStream_t s, unsigned blocks) {
     return dt == PRX_C64
                ? tile_t<float>(B, m, psi, a, rots, chunks, renorm_in, norm_out, s, blocks)
@@ -732,6 +857,39 @@ hipError_t launch_renorm_finish(const double *partials, unsigned count, double *
     }
     hipLaunchKernelGGL(k_renorm_finish, dim3(1), dim3(1024), 0, s, partials, count, scale_out);
     return hipGetLastError();
+}
+
+unsigned resident_threads(int n) { return n > 10 ? 1u << (n - 4) : 64u; }
+
+template <typename T>
+static hipError_t resident_t(void *psi, int n, const void *rots, const void *chunks,
+                             uint32_t begin, uint32_t count, const double *rin, double *rout,
+                             hipStream_t s) {
+    Cx<T> *p = (Cx<T> *)psi;
+    const ChunkRec<T> *c = (const ChunkRec<T> *)chunks + begin;
+    const RotRec<T> *r = (const RotRec<T> *)rots;
+    if (n < kResidentMinQubits || n > resident_max_qubits(sizeof(T) == 4 ? PRX_C64 : PRX_C128))
+        return hipErrorInvalidValue;
+    const dim3 one(1), nt(resident_threads(n));
+    switch (n) {
+    case 11: hipLaunchKernelGGL((k_resident<T, 11>), one, nt, 0, s, p, n, c, count, r, rin, rout); break;
+    case 12: hipLaunchKernelGGL((k_resident<T, 12>), one, nt, 0, s, p, n, c, count, r, rin, rout); break;
+    case 13: hipLaunchKernelGGL((k_resident<T, 13>), one, nt, 0, s, p, n, c, count, r, rin, rout); break;
+    case 14:
+        if constexpr (sizeof(T) == 4)
+            hipLaunchKernelGGL((k_resident<T, 14>), one, nt, 0, s, p, n, c, count, r, rin, rout);
+        break;
+    default: hipLaunchKernelGGL((k_resident<T, 10>), one, nt, 0, s, p, n, c, count, r, rin, rout); break;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_resident(prx_dtype dt, void *psi, int n, const void *rots, const void *chunks,
+                           uint32_t chunk_begin, uint32_t chunk_count, const double *rin,
+                           double *rout, hipStream_t s) {
+    return dt == PRX_C64
+               ? resident_t<float>(psi, n, rots, chunks, chunk_begin, chunk_count, rin, rout, s)
+               : resident_t<double>(psi, n, rots, chunks, chunk_begin, chunk_count, rin, rout, s);
 }
 
 static unsigned reduce_grid(uint64_t N) {

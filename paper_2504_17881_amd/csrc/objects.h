@@ -58,6 +58,14 @@ struct Pass {
     uint8_t pdst[kPermBits] = {};
 };
 
+// A tile chunk on the host: the device record's head, the pending per-slot
+// factors at the chunk's end and the coset labels' factors.
+struct Chunk {
+    ChunkHead h;
+    double fscale[kMaxChunkRank];
+    double fac[32];
+};
+
 struct PlanCfg {
     int B = 12;           // tile qubits
     int m = 4;            // chunk rank (tile)
@@ -71,6 +79,7 @@ struct PlanCfg {
     bool tile_only = false;  // batched plans: every pass is a tile pass
     bool relabel = false;    // qubit-relabelling passes between segments
     unsigned grid_cap = (unsigned)kMaxGridBlocks;  // workgroups per sweep launch
+    bool shaped = false;     // the caller chose frames or spans: no resident plan
 };
 
 // Kernel arguments of a tile pass of a plan for n qubits.
@@ -99,8 +108,10 @@ struct prx_plan {
     prx::PlanCfg cfg;
     std::vector<prx::KRot> rots;
     std::vector<prx::Pass> passes;
-    std::vector<prx::ChunkRec> chunks;
-    std::vector<unsigned char> rot_table;  // RotRec<float> or RotRec<double> image
+    std::vector<prx::Chunk> chunks;
+    std::vector<unsigned char> rot_table;    // RotRec<float> or RotRec<double> image
+    std::vector<unsigned char> chunk_table;  // ChunkRec<float> or ChunkRec<double> image
+    bool resident = false;  // every pass a tile pass of the whole state, run in one launch
     prx::WsLayout ws;
     size_t plain_passes = 0, span_passes = 0, tile_passes = 0;
 };

@@ -170,7 +170,8 @@ static void chunk_complement(const Gf2 &basis_span, int B, int nbits, int bank_b
                              uint16_t *cvec) {
     Gf2 G = basis_span;
     int t = 0;
-    for (int i = 0; i < bank_bits && i < B && t < nbits; ++i) {
+    bank_bits = std::min(bank_bits, B);
+    for (int i = 0; i < bank_bits && t < nbits; ++i) {
         for (uint32_t h = 0; h < (1u << (B - bank_bits)); ++h) {
             const uint32_t c = (1u << i) ^ (h << bank_bits);
             if (!G.contains(c)) {
@@ -395,12 +396,12 @@ struct Builder {
                     basis.push_back(1u << u);
                 }
             }
-            ChunkRec ch;
+            Chunk ch;
             std::memset(&ch, 0, sizeof(ch));
-            ch.rot_begin = (uint32_t)r;
-            ch.rot_count = (uint32_t)(q - r);
-            for (int i = 0; i < cfg.m; ++i) ch.basis[i] = basis[i];
-            chunk_complement(cg, cfg.B, cfg.B - cfg.m, P.dtype == PRX_C64 ? 5 : 4, ch.cvec);
+            ch.h.rot_begin = (uint32_t)r;
+            ch.h.rot_count = (uint32_t)(q - r);
+            for (int i = 0; i < cfg.m; ++i) ch.h.basis[i] = basis[i];
+            chunk_complement(cg, cfg.B, cfg.B - cfg.m, P.dtype == PRX_C64 ? 5 : 4, ch.h.cvec);
             P.chunks.push_back(ch);
             SlotScale ss;
             for (size_t t = r; t < q; ++t) {
@@ -413,14 +414,13 @@ struct Builder {
                 for (int i = 0; i < cfg.m; ++i) zeta |= par((uint64_t)basis[i] & L.z) << i;
                 recs.push_back(ss.record(k, slot, zeta, L.z, L.zhigh, cfg.m));
             }
-            ChunkRec &cb = P.chunks.back();
+            Chunk &cb = P.chunks.back();
             for (int i = 0; i < kMaxChunkRank; ++i) cb.fscale[i] = ss.K[i];
             for (int v = 0; v < (1 << cfg.m) && v < 32; ++v) {
                 double f = 1.0;
                 for (int i = 0; i < cfg.m; ++i)
                     if (v >> i & 1) f *= ss.K[i];
-                cb.facd[v] = f;
-                cb.facf[v] = (float)f;
+                cb.fac[v] = f;
             }
             r = q;
         }
@@ -433,6 +433,13 @@ struct Builder {
 
     void run_plain() {
         for (size_t p = P.begin; p < end; ++p) emit_plain(p);
+    }
+
+    // The whole state in one frame: passes of up to 128 rotations (the most a
+    // pass's unscaled amplitudes are built for).
+    void run_resident() {
+        size_t p = P.begin;
+        while (p < end) p = emit_tile(p, 0);
     }
 
     // Every pass a tile pass (batched tile rounds): from each position the
@@ -713,6 +720,32 @@ static Pass perm_pass(int n, const Layout &A, const Layout &B) {
     return ps;
 }
 
+// Whether a resident plan is expected to take longer than the tile passes it
+// replaces.  Times per piece (us), resident against tile passes, fitted to
+// 500-rotation Trotter, qDRIFT and random sequences:
+//   complex64, 14 qubits: rotation 0.22 / 0.14, chunk 1.0 / 0.6, launch 4.6
+//   complex128, 13:       rotation 0.19 / 0.15, chunk 1.6 / 0.6, launch 5.0
+//   complex128, 12:       rotation 0.14 / 0.14, chunk 1.3 / 0.6, launch 5.0
+// so one CU loses only where many rotations share few frames: a sorted Trotter
+// step at 13 qubits in complex128 takes 210 us resident and 151 us in 9 tile
+// passes; a qDRIFT sequence 251 us against 292 us in 31.  Below these sizes a
+// pass's launch alone outweighs the difference.
+static bool resident_loses(const prx_plan &P) {
+    double rot, chunk, pass;
+    if (P.dtype == PRX_C64 && P.n == 14)
+        rot = 0.08, chunk = 0.4, pass = 4.6;
+    else if (P.dtype == PRX_C128 && P.n >= 12)
+        rot = P.n == 13 ? 0.04 : 0.0, chunk = P.n == 13 ? 1.0 : 0.7, pass = 5.0;
+    else
+        return false;
+    const double more = rot * (double)P.rots.size() + chunk * (double)P.chunks.size();
+    const int B = P.dtype == PRX_C64 ? 12 : 11, g = P.dtype == PRX_C64 ? 8 : 7;
+    // it loses when the passes, less the one launch that it takes itself, cost
+    // less than what it spends more in them
+    const size_t most = (size_t)(more / pass) + 1;
+    return model_passes(P.rots, 0, P.rots.size(), Layout{}, B - g, g, 128, nullptr, most + 1) <= most;
+}
+
 static void default_cfg(prx_dtype dt, PlanCfg &c) {
     c.B = (dt == PRX_C64) ? 12 : 11;
     c.m = 4;
@@ -725,6 +758,8 @@ static void default_cfg(prx_dtype dt, PlanCfg &c) {
 
 static void apply_opts(const prx_plan_opts *o, PlanCfg &c) {
     if (!o) return;
+    if (o->tile_qubits || o->chunk_rank || o->span_max || o->max_virtual || o->tile_only > 0)
+        c.shaped = true;
     if (o->tile_qubits) c.B = o->tile_qubits;
     if (o->chunk_rank) c.m = o->chunk_rank;
     if (o->span_max) c.span_m = o->span_max;
@@ -766,6 +801,16 @@ static void pack_records(prx_plan &P, const std::vector<RotRecD> &recs) {
     }
 }
 
+template <typename T>
+static void pack_chunks(prx_plan &P) {
+    P.chunk_table.resize(P.chunks.size() * sizeof(ChunkRec<T>));
+    ChunkRec<T> *out = reinterpret_cast<ChunkRec<T> *>(P.chunk_table.data());
+    for (size_t i = 0; i < P.chunks.size(); ++i) {
+        out[i].h = P.chunks[i].h;
+        for (int v = 0; v < 32; ++v) out[i].fac[v] = (T)P.chunks[i].fac[v];
+    }
+}
+
 static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtype, size_t begin,
                                    size_t end, prx_kernel kernel, const prx_plan_opts *opts,
                                    const PlanCfg *internal, prx_plan **out) {
@@ -791,6 +836,17 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         apply_opts(opts, P->cfg);
         if (internal) P->cfg = *internal;
         const bool fused = kernel != PRX_PLAIN;
+        // a state that one workgroup's LDS holds, unless the caller asked for
+        // particular frames
+        const PlanCfg tiled = P->cfg;
+        if (fused && !internal && !P->cfg.shaped && n >= kResidentMinQubits &&
+            n <= resident_max_qubits(dtype)) {
+            P->resident = true;
+            P->cfg.B = n;
+            P->cfg.m = 4;
+            P->cfg.max_fuse = std::min(P->cfg.max_fuse, 128);
+            P->cfg.commuting = P->cfg.relabel = false;  // every rotation fits already
+        }
         if (P->cfg.tile_only && (!fused || n < P->cfg.B)) {
             delete P;
             return fail(PRX_ERR_INVALID, "tile_only needs a fused kernel and n >= tile_qubits");
@@ -823,10 +879,25 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         }
         P->end = P->rots.size();
         std::vector<RotRecD> recs;
+        if (P->resident) {
+            Builder bld(*P, P->end);
+            bld.run_resident();
+            if (resident_loses(*P)) {
+                P->resident = false;
+                P->cfg = tiled;
+                P->passes.clear();
+                P->chunks.clear();
+                P->tile_passes = 0;
+            } else {
+                recs.swap(bld.recs);
+            }
+        }
         const bool relabel = P->cfg.relabel && fused && !P->cfg.span_only &&
                              n >= std::max(P->cfg.B + 2, 14) &&
                              tile_supported(dtype, P->cfg.B, P->cfg.m);
-        if (!relabel) {
+        if (P->resident) {
+            // built above
+        } else if (!relabel) {
             Builder bld(*P, P->end);
             // span passes need 2^(n - m) >= 1 cosets; tiny states fall back to plain
             if (P->cfg.span_only)
@@ -912,14 +983,24 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
                 }
             }
         }
-        if (dtype == PRX_C64)
+        if (P->resident)
+            for (const Pass &ps : P->passes) {
+                ChunkHead &h = P->chunks[ps.c1 - 1].h;
+                h.flags = kChunkPassEnd | (ps.renorm_in ? kChunkRenormIn : 0u) |
+                          (ps.norm_out ? kChunkNormOut : 0u);
+                h.scale = ps.scale;
+            }
+        if (dtype == PRX_C64) {
             pack_records<float>(*P, recs);
-        else
+            pack_chunks<float>(*P);
+        } else {
             pack_records<double>(*P, recs);
+            pack_chunks<double>(*P);
+        }
         // workspace layout
         size_t maxblocks = 1;
         for (const Pass &ps : P->passes) {
-            if (!ps.norm_out) continue;
+            if (!ps.norm_out || P->resident) continue;
             const size_t nb = ps.kind == kSpan ? span_blocks(n, ps.m, P->cfg.grid_cap)
                                                : tile_blocks(n, ps.B, P->cfg.grid_cap);
             maxblocks = std::max(maxblocks, nb);
@@ -928,7 +1009,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         w.rot_off = 0;
         w.rot_bytes = P->rot_table.size();
         w.chunk_off = align256(w.rot_off + w.rot_bytes + kRecordReadAhead);
-        w.chunk_bytes = P->chunks.size() * sizeof(ChunkRec);
+        w.chunk_bytes = P->chunk_table.size();
         w.part_off = align256(w.chunk_off + w.chunk_bytes);
         w.scal_bytes = (1 + kRenormStage) * sizeof(double);
         w.direct = (unsigned)std::min<size_t>(maxblocks, kRenormDirect);
@@ -1007,7 +1088,7 @@ prx_status prx_plan_upload(const prx_plan *P, void *ws, size_t ws_bytes, void *s
         PRX_HIP(hipMemcpyAsync(base + P->ws.rot_off, P->rot_table.data(), P->ws.rot_bytes,
                                hipMemcpyHostToDevice, s));
     if (P->ws.chunk_bytes)
-        PRX_HIP(hipMemcpyAsync(base + P->ws.chunk_off, P->chunks.data(), P->ws.chunk_bytes,
+        PRX_HIP(hipMemcpyAsync(base + P->ws.chunk_off, P->chunk_table.data(), P->ws.chunk_bytes,
                                hipMemcpyHostToDevice, s));
     return PRX_OK;
 }
@@ -1026,9 +1107,28 @@ static prx_status execute_impl(const prx_plan *P, void *psi, void *ws, size_t ws
         return fail(PRX_ERR_INVALID, "misaligned state or workspace");
     char *base = (char *)ws;
     const void *rots = base + P->ws.rot_off;
-    const ChunkRec *chunks = (const ChunkRec *)(base + P->ws.chunk_off);
+    const void *chunks = base + P->ws.chunk_off;
     double *part = (double *)(base + P->ws.part_off);
     double *scal = (double *)(base + P->ws.scal_off);
+    if (P->resident) {
+        // one launch for all passes; timed, one launch per pass, the factor
+        // handed on through `scal`
+        const size_t np = P->passes.size();
+        for (size_t i = 0; i < np; i += ev ? 1 : np) {
+            const size_t last = ev ? i : np - 1;
+            const uint32_t c0 = (uint32_t)P->passes[i].c0;
+            if (ev) PRX_HIP(hipEventRecord(ev[3 * i], s));
+            const hipError_t e = launch_resident(
+                P->dtype, psi, P->n, rots, chunks, c0, (uint32_t)P->passes[last].c1 - c0,
+                P->passes[i].renorm_in ? scal : nullptr, P->passes[last].norm_out ? scal : nullptr, s);
+            if (e != hipSuccess) return hip_fail(e, "resident launch");
+            if (ev) {
+                PRX_HIP(hipEventRecord(ev[3 * i + 1], s));
+                PRX_HIP(hipEventRecord(ev[3 * i + 2], s));
+            }
+        }
+        return PRX_OK;
+    }
     auto blocks_of = [&](const Pass &ps) -> unsigned {
         if (ps.kind == kSpan) return span_blocks(P->n, ps.m, P->cfg.grid_cap);
         if (ps.kind == kTile)
@@ -1184,7 +1284,7 @@ prx_status prx_plan_pass(const prx_plan *P, size_t i, prx_pass_info *o) {
         o->block_threads = 256;
     } else {
         o->grid_blocks = tile_blocks(P->n, ps.B, P->cfg.grid_cap);
-        o->block_threads = 1u << (ps.B - ps.m);
+        o->block_threads = P->resident ? resident_threads(P->n) : 1u << (ps.B - ps.m);
     }
     return PRX_OK;
 }
@@ -1192,13 +1292,13 @@ prx_status prx_plan_pass(const prx_plan *P, size_t i, prx_pass_info *o) {
 prx_status prx_plan_chunk(const prx_plan *P, size_t i, prx_chunk_info *o) {
     if (!P || !o) return fail(PRX_ERR_INVALID, "null pointer");
     if (i >= P->chunks.size()) return fail(PRX_ERR_INVALID, "chunk index out of range");
-    const ChunkRec &c = P->chunks[i];
+    const Chunk &c = P->chunks[i];
     std::memset(o, 0, sizeof(*o));
-    for (int k = 0; k < kMaxChunkRank; ++k) o->basis[k] = c.basis[k];
-    for (int k = 0; k < kMaxTileThreadBits; ++k) o->cvec[k] = c.cvec[k];
+    for (int k = 0; k < kMaxChunkRank; ++k) o->basis[k] = c.h.basis[k];
+    for (int k = 0; k < kMaxTileThreadBits; ++k) o->cvec[k] = c.h.cvec[k];
     for (int k = 0; k < kMaxChunkRank; ++k) o->fscale[k] = c.fscale[k];
-    o->rot_begin = c.rot_begin;
-    o->rot_count = c.rot_count;
+    o->rot_begin = c.h.rot_begin;
+    o->rot_count = c.h.rot_count;
     return PRX_OK;
 }
 

@@ -140,6 +140,12 @@ prx_status prx_autotune_progress(void *psi, int n, prx_dtype dtype, const prx_sc
         prx_status st_ = run(o);            \
         if (st_ != PRX_OK) return st_;      \
     } while (0)
+    // States that one workgroup's LDS holds: the default (resident) plan.
+    if (n <= resident_max_qubits(dtype)) {
+        prx_plan_opts o;
+        std::memset(&o, 0, sizeof(o));
+        PRX_TUNE_RUN(o);
+    }
     // Stage 1: every built tile shape (tile qubits B, chunk rank m) with the
     // most virtual qubits it allows.
     std::vector<Shape> shapes_ok;
