@@ -151,7 +151,8 @@ typedef struct {
     int max_fuse;        /* max rotations per tile pass (default 128) */
     int span_max;        /* max rotations per span pass (default: chunk_rank and repeats) */
     int max_virtual;     /* max high-qubit XOR masks gathered into a tile, <= 10; the tile
-                            keeps at least 16 contiguous amplitudes (default 8) */
+                            keeps at least 16 contiguous amplitudes (default 8; where no
+                            tile or span option is given, tile_qubits - 4) */
     int renorm_every;    /* C64: renormalise in FP64 every k passes (default 1; -1 = never) */
     int commuting;       /* 1: planner may swap adjacent commuting rotations (default 0) */
     int tile_only;       /* 1: every pass a tile pass, as batched samples of >= tile_qubits

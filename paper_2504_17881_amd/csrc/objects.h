@@ -77,6 +77,7 @@ struct PlanCfg {
     bool span_only = false;  // batched plans: every pass is a span pass ...
     int pad_rank = 0;        // ... whose basis is padded to exactly this rank
     bool tile_only = false;  // batched plans: every pass is a tile pass
+    bool narrow = true;      // at most n - B virtual qubits per frame
     bool relabel = false;    // qubit-relabelling passes between segments
     unsigned grid_cap = (unsigned)kMaxGridBlocks;  // workgroups per sweep launch
     bool shaped = false;     // the caller chose frames or spans: no resident plan

@@ -47,25 +47,37 @@ static inline bool commute(const KRot &a, const KRot &b) {
     return (popc((a.x & b.z) ^ (a.z & b.x)) & 1) == 0;
 }
 
-// Row-echelon basis over GF(2) with pivot = highest set bit of each row;
-// every row remembers which of the inserted vectors it combines.
+// Row-echelon basis over GF(2), one row per pivot (its highest set bit);
+// every row remembers which of the inserted vectors it combines.  Fixed
+// arrays: the planner builds one per candidate frame and position, and with
+// heap-allocated rows that was most of its time.
 struct Gf2 {
-    std::vector<uint64_t> orig;
-    std::vector<uint64_t> row, comb;
+    uint64_t row[64];   // row[h]: the row of pivot h, valid where `has` has bit h
+    uint64_t comb[64];
+    uint64_t orig[64];
+    uint64_t has = 0;
+    uint32_t count = 0;
+    Gf2() {}
+    Gf2(const Gf2 &o) { *this = o; }
+    Gf2 &operator=(const Gf2 &o) {  // only what is valid
+        has = o.has;
+        count = o.count;
+        std::memcpy(orig, o.orig, count * sizeof(uint64_t));
+        for (uint64_t m = has; m; m &= m - 1) {
+            const int h = __builtin_ctzll(m);
+            row[h] = o.row[h];
+            comb[h] = o.comb[h];
+        }
+        return *this;
+    }
     // reduce v; returns the remainder and the combination of originals used
     uint64_t reduce(uint64_t v, uint64_t *cmb) const {
         uint64_t c = 0;
-        bool again = true;
-        while (v && again) {
-            again = false;
-            for (size_t i = 0; i < row.size(); ++i) {
-                if (hibit(row[i]) == hibit(v)) {
-                    v ^= row[i];
-                    c ^= comb[i];
-                    again = true;
-                    break;
-                }
-            }
+        while (v) {
+            const int h = hibit(v);
+            if (!(has >> h & 1)) break;
+            v ^= row[h];
+            c ^= comb[h];
         }
         if (cmb) *cmb = c;
         return v;
@@ -74,20 +86,22 @@ struct Gf2 {
     // adds v (must be independent); returns its index among originals
     size_t add(uint64_t v) {
         uint64_t c;
-        uint64_t r = reduce(v, &c);
-        const size_t id = orig.size();
-        orig.push_back(v);
-        row.push_back(r);
-        comb.push_back(c ^ (1ull << id));
+        const uint64_t r = reduce(v, &c);
+        const size_t id = count++;
+        const int h = hibit(r);
+        orig[id] = v;
+        row[h] = r;
+        comb[h] = c ^ (1ull << id);
+        has |= 1ull << h;
         return id;
     }
+    // the pivots, ascending
     std::vector<uint32_t> pivots() const {
         std::vector<uint32_t> p;
-        for (uint64_t r : row) p.push_back((uint32_t)hibit(r));
-        std::sort(p.begin(), p.end());
+        for (uint64_t m = has; m; m &= m - 1) p.push_back((uint32_t)__builtin_ctzll(m));
         return p;
     }
-    size_t rank() const { return orig.size(); }
+    size_t rank() const { return count; }
 };
 
 // Tau (signed magnitude of i^{nY+1} tan(phi)) and whether it is imaginary.
@@ -217,14 +231,25 @@ struct Builder {
         return j - p;
     }
 
-    bool tile_fits(uint64_t x, int b, Gf2 &M, int g, bool grow) const {
+    // Whether a rotation fits a frame of b low qubits and masks M (at most g).
+    static bool tile_fits(uint64_t x, int b, const Gf2 &M, int g) {
+        return (int)M.rank() < g || M.contains(x >> b);
+    }
+    // The same, adding the rotation's mask to M.
+    static bool tile_take(uint64_t x, int b, Gf2 &M, int g) {
         const uint64_t xh = x >> b;
-        if (xh == 0 || M.contains(xh)) return true;
-        if ((int)M.rank() < g) {
-            if (grow) M.add(xh);
-            return true;
-        }
-        return false;
+        if (M.contains(xh)) return true;
+        if ((int)M.rank() >= g) return false;
+        M.add(xh);
+        return true;
+    }
+
+    // Most virtual qubits of a frame: masks over the n - b index bits above
+    // the low b = B - g.  tile_only plans, and the batched samples planned as
+    // they are, stop at n - B masks.
+    int most_virtual() const {
+        const int g = std::min(cfg.max_virtual, cfg.B - kMinTileLow);
+        return cfg.narrow ? std::min(g, P.n - cfg.B) : g;
     }
 
     size_t tile_len(size_t p, int g) const {
@@ -232,7 +257,7 @@ struct Builder {
         Gf2 M;
         size_t j = p;
         for (; j < end && (int)(j - p) < cfg.max_fuse; ++j)
-            if (!tile_fits(R[j].x, b, M, g, true)) break;
+            if (!tile_take(R[j].x, b, M, g)) break;
         return j - p;
     }
 
@@ -328,13 +353,10 @@ struct Builder {
         const uint64_t low = (b >= 64) ? ~0ull : ((1ull << b) - 1ull);
         Gf2 M;
         size_t j = p;
-        auto fits = [&](const KRot &r) {
-            Gf2 copy = M;
-            return tile_fits(r.x, b, copy, g, false);
-        };
+        auto fits = [&](const KRot &r) { return tile_fits(r.x, b, M, g); };
         for (; j < stop && (int)(j - p) < cfg.max_fuse; ++j) {
             if (!fits(R[j]) && !pull_forward(j, fits)) break;
-            tile_fits(R[j].x, b, M, g, true);
+            tile_take(R[j].x, b, M, g);
         }
         // Pad the virtual masks to exactly g with unused high unit vectors so
         // that every workgroup holds 2^B amplitudes.
@@ -450,8 +472,7 @@ struct Builder {
         while (p < end) {
             int gbest = -1;
             size_t best = 0;
-            for (int g = 0; g <= cfg.max_virtual && g <= P.n - cfg.B && cfg.B - g >= kMinTileLow;
-                 ++g) {
+            for (int g = 0; g <= most_virtual(); ++g) {
                 const size_t f = tile_len(p, g);
                 if (f > best) {
                     best = f;
@@ -476,7 +497,7 @@ struct Builder {
     Reach reach_from(size_t p, bool tile_ok) const {
         Reach r{p + span_len(p, cfg.span_m), kSpan, 0};
         if (tile_ok) {
-            for (int g = 0; g <= cfg.max_virtual && g <= P.n - cfg.B && cfg.B - g >= kMinTileLow; ++g) {
+            for (int g = 0; g <= most_virtual(); ++g) {
                 const size_t e = p + tile_len(p, g);
                 if (e > r.end) r = Reach{e, kTile, g};
             }
@@ -558,7 +579,7 @@ struct Builder {
             size_t ft = 0;
             int gbest = 0;
             if (tile_ok) {
-                for (int g = 0; g <= cfg.max_virtual && g <= P.n - cfg.B && cfg.B - g >= kMinTileLow; ++g) {
+                for (int g = 0; g <= most_virtual(); ++g) {
                     const size_t f = tile_len(p, g);
                     if (f > ft) {
                         ft = f;
@@ -756,6 +777,22 @@ static void default_cfg(prx_dtype dt, PlanCfg &c) {
     c.commuting = false;
 }
 
+// Frames of a plan whose caller names none, by the size of the state (times
+// in us of 500-rotation qDRIFT sequences).  Small states want workgroups: at
+// 17 qubits complex64 takes 365 with 12-qubit frames (32 workgroups), 374 with
+// 13 and 431 with 14; complex128 376 with 11, 388 with 12.  Larger ones want
+// fewer sweeps: complex64 at 21 qubits 658 / 581 / 642, at 24 (200 rotations)
+// 1060 / 976 / 794; complex128 at 20 qubits 668 with 11 and 598 with 12, at 28
+// (200 rotations) 33709 and 29418 (13-qubit frames: 26317 there, but 9 %
+// slower on a 26-qubit sorted Trotter step).
+static void default_frames(prx_dtype dt, int n, PlanCfg &c) {
+    if (dt == PRX_C64)
+        c.B = n < 19 ? 12 : n < 23 ? 13 : 14;
+    else
+        c.B = n < 18 ? 11 : 12;
+    c.max_virtual = c.B - kMinTileLow;
+}
+
 static void apply_opts(const prx_plan_opts *o, PlanCfg &c) {
     if (!o) return;
     if (o->tile_qubits || o->chunk_rank || o->span_max || o->max_virtual || o->tile_only > 0)
@@ -838,6 +875,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         const bool fused = kernel != PRX_PLAIN;
         // a state that one workgroup's LDS holds, unless the caller asked for
         // particular frames
+        if (fused && !internal && !P->cfg.shaped) default_frames(dtype, n, P->cfg);
         const PlanCfg tiled = P->cfg;
         if (fused && !internal && !P->cfg.shaped && n >= kResidentMinQubits &&
             n <= resident_max_qubits(dtype)) {
@@ -847,6 +885,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             P->cfg.max_fuse = std::min(P->cfg.max_fuse, 128);
             P->cfg.commuting = P->cfg.relabel = false;  // every rotation fits already
         }
+        if (!internal) P->cfg.narrow = P->cfg.tile_only;
         if (P->cfg.tile_only && (!fused || n < P->cfg.B)) {
             delete P;
             return fail(PRX_ERR_INVALID, "tile_only needs a fused kernel and n >= tile_qubits");
