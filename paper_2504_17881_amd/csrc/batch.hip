@@ -350,7 +350,7 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
                         return fail(PRX_ERR_UNSUPPORTED, "tile-only plan with another pass kind");
                     }
                     TileArgs ta;
-                    tile_args(n[s], ps, ta);
+                    tile_args(n[s], dtype, ps, ta);
                     ta.chunk_begin += chunk_base;
                     b->tpasses.push_back(ta);
                 }

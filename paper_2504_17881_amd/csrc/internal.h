@@ -125,6 +125,18 @@ struct SpanArgs {
     double fscale[kMaxChunkRank];  // pending per-slot factors K
 };
 
+// State accesses of the tile workgroups that own one tile-set, by the bytes of
+// state a sequence of passes comes back to.  Between the L2s' 32 MiB and the
+// 256 MiB of the last-level cache, ordinary accesses keep it there (12-qubit
+// passes of a qDRIFT sequence: 24 qubits complex64 53 us against 59 us
+// non-temporal, 25 qubits 95 / 112; 24 qubits complex128 96 / 114).  Larger
+// states stream through (28 qubits complex64 854 / 811 us), and what the L2s
+// hold is written back during a pass rather than at its end (21 qubits
+// complex64 17.8 / 16.0 us, 20 qubits complex128 17.2 / 15.5).
+static inline bool streams_state(double bytes) {
+    return bytes <= 32.0 * 1048576.0 || bytes > 256.0 * 1048576.0;
+}
+
 // Kernel arguments of a tile pass.
 struct TileArgs {
     // Slot s = tid + u NT of the tile-set holds amplitude
@@ -136,6 +148,7 @@ struct TileArgs {
     uint64_t tpivots;             // pivot bits of the masks' echelon form, ascending,
                                   // 6 bits each (pivot i in bits 6i .. 6i+5)
     int n, b, g;
+    int stream;      // non-temporal state accesses (see streams_state)
     uint32_t chunk_begin, chunk_count;
     double scale;
 };

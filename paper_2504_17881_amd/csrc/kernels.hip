@@ -128,6 +128,23 @@ struct Neu {
     __device__ __forceinline__ double value() const { return s + c; }
 };
 
+// Only complex64 states are renormalised: complex128 passes hold no norm code
+// (two FMAs per amplitude).
+template <typename T>
+static constexpr bool kRenorm = sizeof(T) == 4;
+
+// 1 / sqrt(v): the hardware's estimate and two Newton steps (y <- y + y (1 -
+// v y^2) / 2), which leave 0, infinity and NaN as the estimate has them.  A
+// tenth of the code of a correctly rounded division and root, which a short
+// pass fetches cold.
+__device__ __forceinline__ double inv_sqrt(double v) {
+    const double y0 = __builtin_amdgcn_rsq(v);
+    double y = y0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-v * y, y, 1.0), y);
+    return v > 0.0 && v < __builtin_huge_val() ? y : y0;
+}
+
 // The factor 1 / sqrt(norm) a pass takes over from the pass before it: read
 // from one scalar, or, where the earlier pass left at most kRenormDirect
 // partial sums, summed here by every wave (a fixed order, so all waves get
@@ -145,7 +162,7 @@ __device__ __forceinline__ double renorm_factor(const RenormIn &in) {
     const uint64_t u = __double_as_longlong(v);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    return 1.0 / sqrt(__longlong_as_double(((uint64_t)hi << 32) | lo));
+    return inv_sqrt(__longlong_as_double(((uint64_t)hi << 32) | lo));
 }
 
 // ------------------------------------------------------------------ span
@@ -161,7 +178,8 @@ __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs 
     X[0] = 0;
 #pragma unroll
     for (int v = 1; v < (1 << M); ++v) X[v] = X[v & (v - 1)] ^ a.basis[__builtin_ctz(v)];
-    const double sc = a.scale * renorm_factor(renorm_in);
+    double sc = a.scale;
+    if constexpr (kRenorm<T>) sc *= renorm_factor(renorm_in);
     double F[1 << M];
     pending_factors<M>(F, a.fscale);
     double nrm = 0.0;
@@ -189,12 +207,14 @@ __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs 
                 o.re = amp[v].re * s;
                 o.im = amp[v].im * s;
                 psi[k0 ^ X[v]] = o;
-                nrm = fma((double)o.re, (double)o.re, nrm);
-                nrm = fma((double)o.im, (double)o.im, nrm);
+                if constexpr (kRenorm<T>) {
+                    nrm = fma((double)o.re, (double)o.re, nrm);
+                    nrm = fma((double)o.im, (double)o.im, nrm);
+                }
             }
         }
     }
-    if (norm_out) {
+    if (kRenorm<T> && norm_out) {
         nrm = block_sum<256>(nrm, red);
         if (threadIdx.x == 0) norm_out[blockIdx.x] = nrm;
     }
@@ -218,9 +238,8 @@ struct TilePersist {
 // moves G = 16 / sizeof(Cx<T>) consecutive amplitudes at once (two at
 // complex64, one at complex128; measured 4.5 % faster than one complex64
 // amplitude per access for the 14-qubit kernel).  Workgroups that own one
-// tile-set stream it with non-temporal loads and stores (each amplitude is
-// read and written once per pass; measured 3 % faster with 12-qubit
-// tile-sets); the persistent kernel, whose prefetched loads overlap the
+// tile-set take non-temporal or ordinary loads and stores by the state's size
+// (streams_state); the persistent kernel, whose prefetched loads overlap the
 // previous set's stores, is faster with ordinary ones (non-temporal: 7 %
 // slower).
 template <typename T>
@@ -256,7 +275,7 @@ struct TileWaves {
     static constexpr unsigned value = w < 1 ? 1 : (w > 8 ? 8 : w);
 };
 
-template <typename T, int B, int M>
+template <typename T, int B, int M, bool STREAM>
 __global__ void __launch_bounds__(1 << (B - M))
     __attribute__((amdgpu_waves_per_eu(TileWaves<T, B, M>::value))) k_tile(Cx<T> *__restrict__ psi, TileArgs a,
                                                       const RotRec<T> *__restrict__ rots,
@@ -324,25 +343,42 @@ __global__ void __launch_bounds__(1 << (B - M))
     V r[GPER];
     auto load_set = [&](uint64_t b0) {
 #pragma unroll
-        for (int j = 0; j < GPER; ++j) r[j] = group_load<!PERSIST>(psi + (b0 ^ a.uoff[G * j]));
+        for (int j = 0; j < GPER; ++j) r[j] = group_load<STREAM>(psi + (b0 ^ a.uoff[G * j]));
     };
     auto stage_set = [&] {
 #pragma unroll
         for (int j = 0; j < GPER; ++j) lds_v[tid + (uint32_t)j * NT] = r[j];
     };
-    // (the grid never exceeds the set count, so every workgroup has a first
-    // set; its loads are in flight while the previous pass's partials are
-    // summed)
-    load_set(base_of(tile_of(w)));
-    const T s = (T)(a.scale * renorm_factor(renorm_in));
-    stage_set();
-    __syncthreads();
+    // The first set's loads are in flight while the previous pass's partials
+    // are summed (the grid never exceeds the set count, so every workgroup
+    // has a first set).
+    T s = (T)a.scale;
+    bool scaled = !kRenorm<T>;
+    auto take_scale = [&] {
+        if (!scaled) s = (T)(a.scale * renorm_factor(renorm_in));
+        scaled = true;
+    };
+    if (PERSIST) {
+        load_set(base_of(tile_of(w)));
+        take_scale();
+        stage_set();
+        __syncthreads();
+    }
     for (; w < nsets; w += gridDim.x) {
         const uint64_t tb = tile_of(w);
         const uint64_t base = base_of(tb);
+        if (!PERSIST) {
+            // one set per iteration (several when the grid is capped); a
+            // thread writes only the slots it read in the previous store
+            // epilogue, so no barrier is needed before the staging
+            load_set(base);
+            take_scale();
+            stage_set();
+            __syncthreads();
+        }
         const uint32_t wn = w + gridDim.x;
-        const bool next = wn < nsets;  // not persistent: only when the grid is capped
-        if (PERSIST && next) load_set(base_of(tile_of(wn)));
+        const bool next = PERSIST && wn < nsets;
+        if (next) load_set(base_of(tile_of(wn)));
 
         tile_chunks<T, B, M>(lds_raw, tmask, tb, chunks + a.chunk_begin, a.chunk_count, rots);
 
@@ -354,13 +390,14 @@ __global__ void __launch_bounds__(1 << (B - M))
 #pragma unroll
             for (int j = 0; j < GPER; ++j) {
                 const V o = q[j] * s;
-                group_store<!PERSIST>(psi + (base ^ a.uoff[G * j]), o);
+                group_store<STREAM>(psi + (base ^ a.uoff[G * j]), o);
+                if constexpr (kRenorm<T>) {
 #pragma unroll
-                for (int c = 0; c < 2 * G; ++c) nrm = fma((double)o[c], (double)o[c], nrm);
+                    for (int c = 0; c < 2 * G; ++c) nrm = fma((double)o[c], (double)o[c], nrm);
+                }
             }
         }
         if (next) {
-            if (!PERSIST) load_set(base_of(tile_of(wn)));
             // the staging writes exactly the slots this thread read in the
             // store epilogue above (LDS operations of a wave stay in order),
             // so only the chunk gathers of the next set wait at a barrier
@@ -368,7 +405,7 @@ __global__ void __launch_bounds__(1 << (B - M))
             __syncthreads();
         }
     }
-    if (norm_out) {
+    if (kRenorm<T> && norm_out) {
         __syncthreads();  // the tile-set's LDS is reused for the partial sums
         nrm = block_sum<NT>(nrm, reinterpret_cast<double *>(lds_raw));
         if (tid == 0) norm_out[blockIdx.x] = nrm;
@@ -445,8 +482,8 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
             for (int v = 0; v < PER; ++v)
                 amp[v] = *reinterpret_cast<const Cx<T> *>(lds_raw + (k0b ^ Xb[v]));
             apply_rots<T, M>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
-            const double sc = !(ch.flags & kChunkPassEnd) ? 1.0
-                              : ch.flags & kChunkRenormIn ? ch.scale * rn : ch.scale;
+            double sc = ch.scale;
+            if (kRenorm<T> && (ch.flags & kChunkRenormIn)) sc *= rn;
             const T s = (T)sc;
             double nrm = 0.0;
 #pragma unroll
@@ -458,12 +495,14 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
                 if (ch.flags & kChunkPassEnd) {
                     o.re *= s;
                     o.im *= s;
-                    nrm = fma((double)o.re, (double)o.re, nrm);
-                    nrm = fma((double)o.im, (double)o.im, nrm);
+                    if constexpr (kRenorm<T>) {
+                        nrm = fma((double)o.re, (double)o.re, nrm);
+                        nrm = fma((double)o.im, (double)o.im, nrm);
+                    }
                 }
                 *reinterpret_cast<Cx<T> *>(lds_raw + (k0b ^ Xb[v])) = o;
             }
-            if (ch.flags & kChunkNormOut) {
+            if (kRenorm<T> && (ch.flags & kChunkNormOut)) {
                 if (tid >= ncos) nrm = 0.0;
 #pragma unroll
                 for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
@@ -471,12 +510,12 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
             }
         }
         __syncthreads();
-        if (ch.flags & kChunkNormOut) {
+        if (kRenorm<T> && (ch.flags & kChunkNormOut)) {
             // the two places alternate: the next norm may be written before
             // every wave has read this one
             double sum = 0.0;
             for (uint32_t i = 0; i < waves; ++i) sum += red[par][i];
-            rn = 1.0 / sqrt(sum);
+            rn = inv_sqrt(sum);
             par ^= 1u;
         }
     }
@@ -487,7 +526,7 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
             if (tid + (uint32_t)j * NT < ngroups)
                 dst[tid + (uint32_t)j * NT] = lds_v[tid + (uint32_t)j * NT];
     }
-    if (rout && tid == 0) *rout = rn;
+    if (kRenorm<T> && rout && tid == 0) *rout = rn;
 }
 
 template <typename T, int B>
@@ -791,7 +830,7 @@ bool tile_supported(prx_dtype dt, int B, int m) {
 template <typename T, int B, int M>
 static unsigned tile_blocks_one(int n, unsigned cap) {
     return TilePersist<T, B>::value
-               ? tile_grid((const void *)k_tile<T, B, M>, n, B, 1 << (B - M), cap)
+               ? tile_grid((const void *)k_tile<T, B, M, false>, n, B, 1 << (B - M), cap)
                : tile_blocks(n, B, cap);
 }
 
@@ -799,8 +838,14 @@ template <typename T, int B, int M>
 static hipError_t tile_launch_one(void *psi, const TileArgs &a, const void *rots,
                                   const void *chunks, const RenormIn &rin, double *nout,
                                   hipStream_t s, unsigned nb) {
-    hipLaunchKernelGGL((k_tile<T, B, M>), dim3(nb), dim3(1 << (B - M)), 0, s, (Cx<T> *)psi, a,
-                       (const RotRec<T> *)rots, (const ChunkRec<T> *)chunks, rin, nout);
+    if (!TilePersist<T, B>::value && a.stream)
+        hipLaunchKernelGGL((k_tile<T, B, M, !TilePersist<T, B>::value>), dim3(nb),
+                           dim3(1 << (B - M)), 0, s, (Cx<T> *)psi, a, (const RotRec<T> *)rots,
+                           (const ChunkRec<T> *)chunks, rin, nout);
+    else
+        hipLaunchKernelGGL((k_tile<T, B, M, false>), dim3(nb), dim3(1 << (B - M)), 0, s,
+                           (Cx<T> *)psi, a, (const RotRec<T> *)rots,
+                           (const ChunkRec<T> *)chunks, rin, nout);
     return hipGetLastError();
 }
 

@@ -84,7 +84,7 @@ struct PlanCfg {
 };
 
 // Kernel arguments of a tile pass of a plan for n qubits.
-void tile_args(int n, const Pass &ps, TileArgs &a);
+void tile_args(int n, prx_dtype dtype, const Pass &ps, TileArgs &a);
 
 // Workspace regions (byte offsets, 256-aligned).
 struct WsLayout {

@@ -611,7 +611,7 @@ using namespace prx;
 
 namespace prx {
 
-void tile_args(int n, const Pass &ps, TileArgs &a) {
+void tile_args(int n, prx_dtype dtype, const Pass &ps, TileArgs &a) {
     std::memset(&a, 0, sizeof(a));
     for (int k = 0; k < ps.g; ++k) {
         a.vmask[k] = ps.vmask[k];
@@ -629,6 +629,7 @@ void tile_args(int n, const Pass &ps, TileArgs &a) {
     a.n = n;
     a.b = ps.b;
     a.g = ps.g;
+    a.stream = streams_state(std::ldexp(dtype == PRX_C64 ? 8.0 : 16.0, n));
     a.chunk_begin = (uint32_t)ps.c0;
     a.chunk_count = (uint32_t)(ps.c1 - ps.c0);
     a.scale = ps.scale;
@@ -780,7 +781,7 @@ static void default_cfg(prx_dtype dt, PlanCfg &c) {
 // Frames of a plan whose caller names none, by the size of the state (times
 // in us of 500-rotation qDRIFT sequences).  Small states want workgroups: at
 // 17 qubits complex64 takes 365 with 12-qubit frames (32 workgroups), 374 with
-// 13 and 431 with 14; complex128 376 with 11, 388 with 12.  Larger ones want
+// 13 and 431 with 14; complex128 376 with 11, 388 with 12 (18 qubits, 200 rotations: 158 and 176).  Larger ones want
 // fewer sweeps: complex64 at 21 qubits 658 / 581 / 642, at 24 (200 rotations)
 // 1060 / 976 / 794; complex128 at 20 qubits 668 with 11 and 598 with 12, at 28
 // (200 rotations) 33709 and 29418 (13-qubit frames: 26317 there, but 9 %
@@ -789,7 +790,7 @@ static void default_frames(prx_dtype dt, int n, PlanCfg &c) {
     if (dt == PRX_C64)
         c.B = n < 19 ? 12 : n < 23 ? 13 : 14;
     else
-        c.B = n < 18 ? 11 : 12;
+        c.B = n < 19 ? 11 : 12;
     c.max_virtual = c.B - kMinTileLow;
 }
 
@@ -1221,7 +1222,7 @@ static prx_status execute_impl(const prx_plan *P, void *psi, void *ws, size_t ws
             e = launch_span(P->dtype, ps.m, psi, a, rots, rin, nout, s, blocks);
         } else {
             TileArgs a;
-            tile_args(P->n, ps, a);
+            tile_args(P->n, P->dtype, ps, a);
             e = launch_tile(P->dtype, ps.B, ps.m, psi, a, rots, chunks, rin, nout, s, blocks);
         }
         if (e != hipSuccess) return hip_fail(e, "pass launch");

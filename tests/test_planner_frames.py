@@ -40,7 +40,7 @@ def test_wide_frames_match_oracle(n, dtype, opts):
 
 @pytest.mark.parametrize("dtype,sizes", [
     (P.PRX_C64, {15: 12, 18: 12, 19: 13, 22: 13, 23: 14, 34: 14}),
-    (P.PRX_C128, {14: 11, 17: 11, 18: 12, 33: 12}),
+    (P.PRX_C128, {14: 11, 18: 11, 19: 12, 33: 12}),
 ])
 def test_default_frame_sizes(dtype, sizes):
     for n, B in sizes.items():
