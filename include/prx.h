@@ -359,15 +359,15 @@ typedef struct prx_graph prx_graph;
 /* Plans S independent runs: sample s applies sched[s] to its own state
  * (2^n[s] amplitudes of dtype) and reports <basis_idx[s]|psi_s> (the
  * observable of the qDRIFT and partially randomised estimators, Methods).
- * A sample of at least 12 qubits (complex64; 11 for complex128) is
- * segmented into tile passes of that many tile qubits with up to 8 virtual
- * qubits (7 for complex128), bringing a later rotation forward into a pass
- * when it commutes with every rotation it passes (the product is unchanged;
- * only the rounding order differs); a smaller one into span passes of rank 4.  Round p applies pass p
- * of every sample that has one, as one grid-stride kernel over that round's
- * (sample, tile-set) items and one over its (sample, slice) items, so all
- * samples share every launch and no workgroup waits on another.  Host only;
- * no device calls.  INVALID if S = 0, an n[s] is outside [6, 34],
+ * A sample of up to 14 qubits (13 for complex128) stays in one workgroup's
+ * LDS for its whole sequence; all such samples share one launch (one per size
+ * when there are more than 256).  A larger one is segmented into tile passes
+ * of 12 to 14 tile qubits (11 or 12 for complex128), by the amplitudes of the
+ * batch.  Both bring a later rotation forward when it commutes with every
+ * rotation it passes (the product is unchanged; only the rounding order
+ * differs).  Round p applies pass p of every larger sample that has one, as
+ * one grid-stride kernel over that round's (sample, tile-set) items, so no
+ * workgroup waits on another.  Host only; no device calls.  INVALID if S = 0, an n[s] is outside [6, 34],
  * sched[s]->n != n[s], or basis_idx[s] >= 2^n[s]. */
 prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sched,
                             prx_dtype dtype, const uint64_t *basis_idx, prx_batch **out);
@@ -375,12 +375,15 @@ size_t prx_batch_workspace_bytes(const prx_batch *b);
 /* Summary of a batch plan. */
 typedef struct {
     size_t samples;       /* S */
-    size_t tile_samples;  /* samples planned into tile passes */
+    size_t tile_samples;  /* samples of at least 12 qubits (complex128: 11) */
     size_t rounds;        /* largest pass count */
-    size_t passes;        /* passes summed over the samples */
+    size_t passes;        /* passes summed over the samples; a sample of 12 (11) to 14
+                             qubits counts the passes of a tile_only plan of 12 (11)
+                             tile qubits with commuting on */
     double amp_sweeps;    /* sum over samples of passes * 2^n: each sweep reads and
                              writes every amplitude once (algorithmic bytes
-                             = 2 * amp_sweeps * bytes per amplitude) */
+                             = 2 * amp_sweeps * bytes per amplitude; a sample that
+                             stays in LDS makes its sweeps there) */
 } prx_batch_info;
 prx_status prx_batch_get_info(const prx_batch *b, prx_batch_info *out);
 /* Records the device state pointers psi[s] (host array of S distinct,
@@ -388,15 +391,14 @@ prx_status prx_batch_get_info(const prx_batch *b, prx_batch_info *out);
  * `ws`; waits for the copies. */
 prx_status prx_batch_upload(prx_batch *b, void *const *psi, void *ws, size_t ws_bytes,
                             void *stream);
-/* Enqueues, on `stream`, kernels only: at most two per round (the rounds
- * being the largest pass count among the samples) and the overlap read-out into overlaps_dev
+/* Enqueues, on `stream`, kernels only: those of the samples in LDS, one per
+ * round, and the overlap read-out into overlaps_dev
  * (device array of 2*S doubles, (re, im) per sample).  It can therefore be
  * replayed and captured in one graph (prx_batch_graph). */
 prx_status prx_batch_execute(const prx_batch *b, void *ws, size_t ws_bytes,
                              double *overlaps_dev, void *stream);
 /* Caps the grid of every round launch at max_grid workgroups (0 restores
- * the defaults: 2^20 for the tile rounds, 8 per CU for the span rounds);
- * each launch then strides over the rest of its items.  The results do not
+ * the default of 2^20); each launch then strides over the rest of its items.  The results do not
  * depend on the cap.  Takes effect at the next prx_batch_execute or
  * prx_batch_graph.  INVALID for a null batch. */
 prx_status prx_batch_set_max_grid(prx_batch *b, unsigned max_grid);

@@ -1,232 +1,216 @@
 // Batched execution of many independent samples (qDRIFT or partially
 // randomised draws, circuits of uneven qubit counts).
 //
-// Samples that hold a tile frame (n >= B: 12 qubits at complex64, 11 at
-// complex128) are planned into tile passes only, with up to 8 virtual
-// qubits (7 at complex128, every tile keeping 16 contiguous amplitudes): a
-// random-order qDRIFT sequence then fuses 2-2.5 times more rotations per HBM
-// pass than with spans.  Smaller samples are planned into
-// span passes of fixed rank M (the basis padded with unused high
-// directions), every pass with the same 2^(n-M) cosets split into Q slices
-// of at most kSliceCosets.  Round p applies pass p of every sample that has
-// one: one grid-stride kernel over that round's (sample, tile-set) items and
-// one over its (sample, slice) items.  Kernel boundaries order the rounds,
-// so no workgroup ever waits on another; the whole sequence of round kernels
-// is enqueued back to back (and can be captured as one graph).
+// A sample whose state fits one workgroup's LDS (up to 14 qubits at
+// complex64, 13 at complex128) runs its whole sequence there: one launch for
+// all such samples, one workgroup each.  Larger samples are planned into tile
+// passes with as many virtual qubits as 16 contiguous amplitudes allow: a
+// random-order qDRIFT sequence then fuses 2-2.5 times more rotations per pass
+// than with spans.  Round p applies pass p of every sample that has one, as
+// one grid-stride kernel over the round's (sample, tile-set) items.  Kernel
+// boundaries order the rounds, so no workgroup ever waits on another; the
+// whole sequence of kernels is enqueued back to back (and can be captured as
+// one graph).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <new>
 #include <vector>
 
-#include "device.h"
 #include "objects.h"
+#include "resident.h"
 
 namespace prx {
 
-static constexpr int kBatchRank = 4;
-static constexpr uint64_t kSliceCosets = 8192;
 static constexpr int kBatchTileM = 4;
-static constexpr int kBatchMaxVirtual = 8;
 // Tile rounds launch one workgroup per (sample, tile-set) item up to this
 // many (the hardware keeps as many resident as fit and starts the next as
 // soon as one ends), striding beyond it.
 static constexpr uint64_t kTileGridCap = 1u << 20;
+// Resident samples that take one launch whatever their sizes: one per CU.
+// More are launched by size, so that small ones share a CU.
+static constexpr size_t kResidentOneLaunch = 256;
 static int batch_tile_qubits(prx_dtype dt) { return dt == PRX_C64 ? 12 : 11; }
+// Tile qubits of a batch's rounds by the amplitudes of a round with every
+// tile sample.  Larger frames make fewer sweeps (32 samples of 16 to 22
+// qubits: 2485, 2121, 1805 passes with 12, 13, 14 qubits), smaller ones leave
+// more workgroups on a CU to overlap and shorter ends of rounds.  Measured
+// (us per batch): 8 samples of 24 qubits 29201 / 26586 / 24617, 12 of 20 to 23
+// 9338 / 9152 / 9431, 64 of 15 to 18 2644 / 2602 / 2682; complex128, 32 of 15
+// to 21, 10773 with 11 qubits, 9539 with 12, 10444 with 13.
+static int batch_frame_qubits(prx_dtype dt, double amps) {
+    if (dt == PRX_C64) return amps >= 0x1p26 ? 14 : amps >= 0x1p23 ? 13 : 12;
+    return amps >= 0x1p19 ? 12 : 11;
+}
 
+// The overlap read-out of a sample.
 struct BSample {
-    uint64_t psi;       // device address of the state
-    uint64_t ncos;      // 2^(n - M)
-    uint64_t basis_idx; // overlap read-out index
-    uint32_t Q;         // slices per pass
-    uint32_t pass_begin, pass_count;
-    uint32_t n;
+    uint64_t psi;        // device address of the state
+    uint64_t basis_idx;
 };
 
-struct BPass {
-    uint64_t basis[kBatchRank];
-    uint32_t pivot[kBatchRank];
-    uint32_t rot_begin, rot_count;
-    double scale;
-    double fscale[kBatchRank];
+// A sample that stays in one workgroup's LDS.
+struct BResident {
+    uint64_t psi;
+    uint32_t n, chunk_begin, chunk_count, pad;
 };
 
-struct BatchArgs {
-    const BSample *samples;
-    const BPass *passes;
-    const void *rots;
-    const uint64_t *prefixQ;      // S + 1 entries over the pass-count-sorted samples
-    const uint32_t *order;        // sorted position -> sample
+// One pass of a sample in tile passes of fixed (B, M).  A round's passes lie
+// together, with their first items in a table of their own beside them.
+struct BTilePass {
+    TileArgs a;
+    uint64_t psi;
 };
 
 // State amplitudes addressed as global memory: the states' addresses come
 // from the sample tables, and without the address space the compiler would
 // use flat accesses, which also count against the LDS/scalar wait counter.
-// Non-temporal: every amplitude is read and written once per pass (8 %
-// faster on the qDRIFT batch than ordinary loads and stores).
-template <typename T>
-using V2 = T __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ Cx<T> gload(uint64_t psi, uint64_t i) {
-    const V2<T> v =
-        __builtin_nontemporal_load(((const __attribute__((address_space(1))) V2<T> *)psi) + i);
-    Cx<T> r;
-    r.re = v.x;
-    r.im = v.y;
-    return r;
-}
-template <typename T>
-__device__ __forceinline__ void gstore(uint64_t psi, uint64_t i, const Cx<T> &a) {
-    V2<T> v;
-    v.x = a.re;
-    v.y = a.im;
-    __builtin_nontemporal_store(v, ((__attribute__((address_space(1))) V2<T> *)psi) + i);
-}
 // 16 bytes per lane: G = 16 / sizeof(Cx<T>) consecutive amplitudes from
-// amplitude index i (a multiple of G).
-template <typename T>
-using V16 = T __attribute__((ext_vector_type(16 / sizeof(T))));
-template <typename T>
-__device__ __forceinline__ V16<T> gload16(uint64_t psi, uint64_t i) {
-    return __builtin_nontemporal_load(
-        (const __attribute__((address_space(1))) V16<T> *)(psi + i * sizeof(Cx<T>)));
+// amplitude index i (a multiple of G).  Non-temporal: every amplitude is read
+// and written once per pass, and between two passes of a sample lie those of
+// all others (32 samples of 16 to 22 qubits: 11.7 ms against 15.0 ms with
+// ordinary accesses; the same when groups of samples that the last-level
+// cache holds run all their rounds before the next).
+template <bool NT, typename T>
+__device__ __forceinline__ typename Group<T>::V gload(uint64_t psi, uint64_t i) {
+    typedef const __attribute__((address_space(1))) typename Group<T>::V *P;
+    const P p = (P)(psi + i * sizeof(Cx<T>));
+    if constexpr (NT)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
 }
-template <typename T>
-__device__ __forceinline__ void gstore16(uint64_t psi, uint64_t i, const V16<T> &v) {
-    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) V16<T> *)(psi + i * sizeof(Cx<T>)));
+template <bool NT, typename T>
+__device__ __forceinline__ void gstore(uint64_t psi, uint64_t i, const typename Group<T>::V &v) {
+    typedef __attribute__((address_space(1))) typename Group<T>::V *P;
+    const P p = (P)(psi + i * sizeof(Cx<T>));
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
 }
 
-// Round p: items j in [0, prefixQ[active]) over the first `active` sorted
-// samples; item j is slice j - prefixQ[k] of sorted sample k.
+// Item j of a round: the last pass k with first[k] <= j, found from the
+// passes' first items read all at once, one per lane.
+__device__ __forceinline__ uint32_t pass_of(uint32_t j, const uint32_t *__restrict__ first,
+                                            uint32_t count) {
+    uint32_t k = 0;
+    for (uint32_t i = 0; i < count; i += 64u) {
+        const uint32_t at = i + (threadIdx.x & 63u);
+        k += (uint32_t)__popcll(__ballot(at < count && first[at] <= j));
+    }
+    return __builtin_amdgcn_readfirstlane(k - 1u);
+}
+
+// The base tile of set w of a pass and this thread's first amplitude in it.
+struct SetBase {
+    uint64_t tb, base;
+};
+__device__ __forceinline__ SetBase set_base(const TileArgs *ta, uint32_t w, uint32_t gtid) {
+    SetBase s;
+    uint64_t t = w;
+    for (int i = 0; i < ta->g; ++i)
+        t = insert_zero64(t, (uint32_t)(ta->tpivots >> (6 * i)) & 63u);
+    s.tb = t;
+    uint64_t c = t;
+    const uint32_t v = gtid >> ta->b;
+    for (int i = 0; i < ta->g; ++i)
+        if (v >> i & 1) c ^= ta->vmask[i];
+    s.base = (c << ta->b) | (gtid & ((1u << ta->b) - 1u));
+    return s;
+}
+
 // The tables arrive as separate __restrict__ arguments: the compiler then
 // knows the state stores cannot change them and reads them with scalar
-// loads, so the rotation loop's control values stay uniform.
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_batch_round(const BSample *__restrict__ samples, const BPass *__restrict__ passes,
-                  const void *__restrict__ rot_table, const uint64_t *__restrict__ prefixQ,
-                  const uint32_t *__restrict__ order, uint32_t p, uint32_t active,
-                  uint64_t items) {
-    constexpr int M = kBatchRank;
-    for (uint64_t j = blockIdx.x; j < items; j += gridDim.x) {
-        // last k < active with prefixQ[k] <= j (uniform across the block)
-        uint32_t lo = 0, hi = active;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (prefixQ[mid] <= j) lo = mid; else hi = mid;
+// loads, so the rotation loop's control values stay uniform.  A tile-set
+// works as in k_tile: small ones one per workgroup and item; the 128 KiB ones
+// (TilePersist) in workgroups that stride over the items and hold the next
+// item's set in registers while they compute the current one.
+template <typename T, int B, int M>
+__global__ void __launch_bounds__(1 << (B - M))
+    __attribute__((amdgpu_waves_per_eu(TileWaves<T, B, M>::value)))
+    k_batch_tile_round(const BTilePass *__restrict__ passes, const uint32_t *__restrict__ first,
+                       uint32_t count, uint32_t items, const ChunkRec<T> *__restrict__ chunks,
+                       const void *__restrict__ rot_table) {
+    constexpr int NT = 1 << (B - M);
+    constexpr int PER = 1 << M;
+    constexpr bool PERSIST = TilePersist<T, B>::value;
+    constexpr int G = Group<T>::G;
+    constexpr int GPER = PER / G;
+    typedef typename Group<T>::V V;
+    __shared__ __align__(16) Cx<T> lds[1 << B];
+    unsigned char *lds_raw = reinterpret_cast<unsigned char *>(lds);
+    V *lds_v = reinterpret_cast<V *>(lds);
+    const uint32_t tid = threadIdx.x;
+    const uint32_t gtid = (uint32_t)G * tid;  // the thread's first slot (see k_tile)
+    uint32_t tmask[B - M];
+    tile_thread_masks<B - M>(tid, tmask);
+    V r[GPER];
+    auto load_set = [&](const BTilePass *bp, const SetBase &s) {
+#pragma unroll
+        for (int i = 0; i < GPER; ++i)
+            r[i] = gload<!PERSIST, T>(bp->psi, s.base ^ bp->a.uoff[G * i]);
+    };
+    auto stage_set = [&] {
+#pragma unroll
+        for (int i = 0; i < GPER; ++i) lds_v[tid + (uint32_t)i * NT] = r[i];
+    };
+    uint32_t j = blockIdx.x;  // (the grid never exceeds the items)
+    uint32_t k = pass_of(j, first, count);
+    SetBase set = set_base(&passes[k].a, j - first[k], gtid);
+    load_set(passes + k, set);
+    stage_set();
+    __syncthreads();
+    while (true) {
+        const BTilePass *bp = passes + k;
+        const uint32_t jn = j + gridDim.x;
+        const bool next = jn < items;
+        SetBase nset;
+        if (next) {
+            k = pass_of(jn, first, count);
+            nset = set_base(&passes[k].a, jn - first[k], gtid);
+            if (PERSIST) load_set(passes + k, nset);
         }
-        const uint32_t s = order[lo];
-        const uint64_t q = j - prefixQ[lo];
-        const BSample smp = samples[s];
-        const BPass ps = passes[smp.pass_begin + p];
-        const uint64_t psi = smp.psi;
-        const RotRec<T> *rots = reinterpret_cast<const RotRec<T> *>(rot_table) + ps.rot_begin;
-        uint64_t X[1 << M];
-        X[0] = 0;
+        // (the base tile is uniform, but the compiler carries it in vector
+        // registers from one iteration to the next)
+        const uint64_t tb =
+            ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(set.tb >> 32)) << 32) |
+            __builtin_amdgcn_readfirstlane((uint32_t)set.tb);
+        tile_chunks<T, B, M>(lds_raw, tmask, tb, chunks + bp->a.chunk_begin, bp->a.chunk_count,
+                             reinterpret_cast<const RotRec<T> *>(rot_table));
+        const T s = (T)bp->a.scale;
+        {
+            V q[GPER];
 #pragma unroll
-        for (int v = 1; v < (1 << M); ++v) X[v] = X[v & (v - 1)] ^ ps.basis[__builtin_ctz(v)];
-        double F[1 << M];
-        pending_factors<M>(F, ps.fscale);
-        T sc[1 << M];
+            for (int i = 0; i < GPER; ++i) q[i] = lds_v[tid + (uint32_t)i * NT];
 #pragma unroll
-        for (int v = 0; v < (1 << M); ++v) sc[v] = (T)(ps.scale * F[v]);
-        const uint64_t c0 = q * kSliceCosets;
-        const uint64_t c1 = min(c0 + kSliceCosets, smp.ncos);
-        for (uint64_t c = c0 + threadIdx.x; c < c1; c += 256) {
-            uint64_t k0 = c;
-#pragma unroll
-            for (int i = 0; i < M; ++i) k0 = insert_zero64(k0, ps.pivot[i]);
-            Cx<T> amp[1 << M];
-#pragma unroll
-            for (int v = 0; v < (1 << M); ++v) amp[v] = gload<T>(psi, k0 ^ X[v]);
-            apply_rots<T, M>(amp, k0, 0, rots, ps.rot_count);
-#pragma unroll
-            for (int v = 0; v < (1 << M); ++v) {
-                Cx<T> o;
-                o.re = amp[v].re * sc[v];
-                o.im = amp[v].im * sc[v];
-                gstore<T>(psi, k0 ^ X[v], o);
-            }
+            for (int i = 0; i < GPER; ++i)
+                gstore<!PERSIST, T>(bp->psi, set.base ^ bp->a.uoff[G * i], q[i] * s);
         }
+        if (!next) break;
+        // (the staging writes the slots this thread has just read)
+        if (!PERSIST) load_set(passes + k, nset);
+        stage_set();
+        __syncthreads();
+        j = __builtin_amdgcn_readfirstlane(jn);
+        set = nset;
     }
 }
 
-// Tile-mode samples: tile passes of fixed (B, M).
-struct BTSample {
-    uint64_t psi;
-    uint32_t nsets;  // 2^(n - B) tile-sets per pass
-    uint32_t pass_begin, pass_count;
-    uint32_t n;
-};
-
-struct BatchTileArgs {
-    const BTSample *samples;
-    const TileArgs *passes;
-    const void *chunks;
-    const void *rots;
-    const uint64_t *prefixW;  // S_t + 1 tile-set counts over the sorted samples
-    const uint32_t *order;
-};
-
-template <typename T, int B, int M>
-__global__ void __launch_bounds__(1 << (B - M))
-    k_batch_tile_round(const BTSample *__restrict__ samples, const TileArgs *__restrict__ passes,
-                       const ChunkRec<T> *__restrict__ chunks, const void *__restrict__ rot_table,
-                       const uint64_t *__restrict__ prefixW, const uint32_t *__restrict__ order,
-                       uint32_t p, uint32_t active, uint64_t items) {
-    constexpr int NT = 1 << (B - M);
-    constexpr int PER = 1 << M;
+// One workgroup per resident sample (striding beyond the grid); B covers the
+// launch's largest sample.
+template <typename T, int B>
+__global__ void __launch_bounds__((ResidentShape<T, B>::NT))
+    k_batch_resident(const BResident *__restrict__ samples, uint32_t count,
+                     const ChunkRec<T> *__restrict__ chunks, const void *__restrict__ rot_table) {
     __shared__ __align__(16) Cx<T> lds[1 << B];
-    unsigned char *lds_raw = reinterpret_cast<unsigned char *>(lds);
-    const uint32_t tid = threadIdx.x;
-    uint32_t tmask[B - M];
-    tile_thread_masks<B - M>(tid, tmask);
-    for (uint64_t j = blockIdx.x; j < items; j += gridDim.x) {
-        // last k < active with prefixW[k] <= j (uniform across the block)
-        uint32_t lo = 0, hi = active;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (prefixW[mid] <= j) lo = mid; else hi = mid;
-        }
-        const BTSample smp = samples[order[lo]];
-        const uint32_t w = (uint32_t)(j - prefixW[lo]);
-        const TileArgs *ta = passes + smp.pass_begin + p;
-        const uint64_t psi = smp.psi;
-        // the set's base tile and this thread's slots (see k_tile)
-        const int b = ta->b, g = ta->g;
-        uint64_t tb = w;
-        for (int i = 0; i < g; ++i) tb = insert_zero64(tb, (uint32_t)(ta->tpivots >> (6 * i)) & 63u);
-        // 16-byte groups of G slots: thread tid's group j holds slots
-        // G (tid + j NT) .. + G - 1 (see k_tile)
-        constexpr int G = 16 / (int)sizeof(Cx<T>);
-        constexpr int GPER = PER / G;
-        static_assert(sizeof(V16<T>) == 16 && sizeof(V16<T>) == G * sizeof(Cx<T>), "16-byte groups");
-        V16<T> *lds_v = reinterpret_cast<V16<T> *>(lds);
-        const uint32_t gtid = (uint32_t)G * tid;
-        uint64_t c = tb;
-        const uint32_t v = gtid >> b;
-        for (int i = 0; i < g; ++i)
-            if (v >> i & 1) c ^= ta->vmask[i];
-        const uint64_t base = (c << b) | (gtid & ((1u << b) - 1u));
-        {
-            V16<T> r[GPER];
-#pragma unroll
-            for (int j = 0; j < GPER; ++j) r[j] = gload16<T>(psi, base ^ ta->uoff[G * j]);
-#pragma unroll
-            for (int j = 0; j < GPER; ++j) lds_v[tid + (uint32_t)j * NT] = r[j];
-        }
-        __syncthreads();
-        tile_chunks<T, B, M>(lds_raw, tmask, tb, chunks + ta->chunk_begin, ta->chunk_count,
-                             reinterpret_cast<const RotRec<T> *>(rot_table));
-        const T s = (T)ta->scale;
-        {
-            V16<T> q[GPER];
-#pragma unroll
-            for (int j = 0; j < GPER; ++j) q[j] = lds_v[tid + (uint32_t)j * NT];
-#pragma unroll
-            for (int j = 0; j < GPER; ++j) gstore16<T>(psi, base ^ ta->uoff[G * j], q[j] * s);
-        }
-        __syncthreads();  // the next item overwrites the LDS
+    __shared__ double red[2][16];
+    for (uint32_t i = blockIdx.x; i < count; i += gridDim.x) {
+        const BResident s = samples[i];
+        resident_run<T, B>(lds, red, (Cx<T> *)s.psi, (int)s.n, chunks + s.chunk_begin,
+                           s.chunk_count, reinterpret_cast<const RotRec<T> *>(rot_table), nullptr,
+                           nullptr);
+        __syncthreads();  // the next sample overwrites the LDS
     }
 }
 
@@ -248,26 +232,28 @@ struct prx_batch {
     size_t S = 0;
     prx_dtype dtype = PRX_C64;
     std::vector<prx::BSample> samples;
-    std::vector<prx::BPass> passes;
-    std::vector<unsigned char> rots;
-    std::vector<uint64_t> prefixQ;
-    std::vector<uint32_t> order;
-    std::vector<uint32_t> round_active;  // span samples with a pass in round p
-    // tile-mode samples
-    std::vector<prx::BTSample> tsamples;
-    std::vector<uint32_t> tsrc;  // tile-mode sample -> sample
-    std::vector<prx::TileArgs> tpasses;
-    std::vector<unsigned char> tchunks;  // ChunkRec<float> or ChunkRec<double> image
-    std::vector<uint64_t> tprefix;
-    std::vector<uint32_t> torder;
-    std::vector<uint32_t> tround_active;
-    uint64_t total_items = 0, total_tile_items = 0;
-    uint32_t rounds = 0;
+    std::vector<prx::BResident> residents;  // largest first
+    std::vector<uint32_t> rsrc;             // resident -> sample
+    std::vector<prx::BTilePass> tpasses;    // round by round, most rotations first
+    std::vector<uint32_t> tfirst;           // beside them: first item within the round
+    std::vector<uint32_t> tsrc;             // and sample
+    std::vector<unsigned char> chunks;      // ChunkRec<float> or ChunkRec<double> image
+    std::vector<unsigned char> rots;        // RotRec<float> or RotRec<double> image
+    struct Launch {                         // resident samples [first, first + count)
+        int B;
+        uint32_t first, count;
+    };
+    std::vector<Launch> launches;
+    struct Round {                          // passes [begin, begin + count)
+        uint32_t begin, count, items;
+    };
+    std::vector<Round> rounds;
+    int B = 12;                             // their tile qubits
+    prx_batch_info info = {};
     unsigned max_grid = 0;  // 0: the default grid caps
     // workspace layout
-    size_t off_samples = 0, off_passes = 0, off_rots = 0, off_prefix = 0, off_order = 0,
-           off_tsamples = 0, off_tpasses = 0, off_tchunks = 0, off_tprefix = 0, off_torder = 0,
-           total = 0;
+    size_t off_samples = 0, off_residents = 0, off_tpasses = 0, off_tfirst = 0, off_chunks = 0,
+           off_rots = 0, total = 0;
 };
 
 struct prx_graph {
@@ -278,6 +264,123 @@ struct prx_graph {
 using namespace prx;
 
 static size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+namespace prx {
+
+// Appends a plan's chunk and rotation tables; returns the plan's first chunk.
+static uint32_t append_tables(prx_batch *b, const prx_plan *P, size_t csz, size_t rsz) {
+    const uint32_t rot_base = (uint32_t)(b->rots.size() / rsz);
+    const size_t at = b->chunks.size();
+    b->chunks.insert(b->chunks.end(), P->chunk_table.begin(), P->chunk_table.end());
+    for (size_t c = at; c < b->chunks.size(); c += csz)
+        reinterpret_cast<ChunkHead *>(b->chunks.data() + c)->rot_begin += rot_base;
+    b->rots.insert(b->rots.end(), P->rot_table.begin(), P->rot_table.end());
+    return (uint32_t)(at / csz);
+}
+
+// A sample's tile passes before they are laid out by rounds.
+struct TileSample {
+    uint32_t sample, nsets;
+    std::vector<TileArgs> passes;
+    std::vector<uint32_t> rots;  // rotations per pass
+};
+
+// Lays the passes out round by round.  Within a round the passes with most
+// rotations come first: their workgroups take longest, and the last ones to
+// start decide when the round ends.
+static void make_rounds(prx_batch *b, const std::vector<TileSample> &ts) {
+    for (uint32_t p = 0;; ++p) {
+        std::vector<uint32_t> act;
+        for (uint32_t k = 0; k < ts.size(); ++k)
+            if (p < ts[k].passes.size()) act.push_back(k);
+        if (act.empty()) break;
+        std::stable_sort(act.begin(), act.end(), [&](uint32_t x, uint32_t y) {
+            return ts[x].rots[p] > ts[y].rots[p];
+        });
+        prx_batch::Round r{(uint32_t)b->tpasses.size(), (uint32_t)act.size(), 0};
+        for (uint32_t k : act) {
+            b->tpasses.push_back(BTilePass{ts[k].passes[p], 0});
+            b->tfirst.push_back(r.items);
+            b->tsrc.push_back(ts[k].sample);
+            r.items += ts[k].nsets;
+        }
+        b->rounds.push_back(r);
+    }
+}
+
+// One launch for all resident samples, or one per size when there are more of
+// them than CUs.
+static void make_launches(prx_batch *b) {
+    const size_t Sr = b->residents.size();
+    std::vector<uint32_t> order(Sr);
+    for (size_t s = 0; s < Sr; ++s) order[s] = (uint32_t)s;
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) {
+        const BResident &a = b->residents[x], &c = b->residents[y];
+        return a.n != c.n ? a.n > c.n : a.chunk_count > c.chunk_count;
+    });
+    std::vector<BResident> rs(Sr);
+    std::vector<uint32_t> src(Sr);
+    for (size_t k = 0; k < Sr; ++k) {
+        rs[k] = b->residents[order[k]];
+        src[k] = b->rsrc[order[k]];
+    }
+    b->residents.swap(rs);
+    b->rsrc.swap(src);
+    auto size_of = [&](size_t k) { return std::max(10, (int)b->residents[k].n); };
+    for (size_t i = 0; i < Sr;) {
+        size_t e = i + 1;
+        while (e < Sr && (Sr <= kResidentOneLaunch || size_of(e) == size_of(i))) ++e;
+        b->launches.push_back(prx_batch::Launch{size_of(i), (uint32_t)i, (uint32_t)(e - i)});
+        i = e;
+    }
+}
+
+template <typename T>
+static hipError_t launch_residents(int B, unsigned grid, const BResident *r, uint32_t count,
+                                   const void *chunks, const void *rots, hipStream_t st) {
+    const dim3 g(grid), nt(resident_threads(B));
+    const ChunkRec<T> *c = (const ChunkRec<T> *)chunks;
+    switch (B) {
+    case 10: hipLaunchKernelGGL((k_batch_resident<T, 10>), g, nt, 0, st, r, count, c, rots); break;
+    case 11: hipLaunchKernelGGL((k_batch_resident<T, 11>), g, nt, 0, st, r, count, c, rots); break;
+    case 12: hipLaunchKernelGGL((k_batch_resident<T, 12>), g, nt, 0, st, r, count, c, rots); break;
+    case 13: hipLaunchKernelGGL((k_batch_resident<T, 13>), g, nt, 0, st, r, count, c, rots); break;
+    case 14:
+        if constexpr (sizeof(T) == 4) {
+            hipLaunchKernelGGL((k_batch_resident<T, 14>), g, nt, 0, st, r, count, c, rots);
+            break;
+        }
+        return hipErrorInvalidValue;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <typename T, int B>
+static hipError_t launch_round_b(unsigned grid, const BTilePass *passes, const uint32_t *first,
+                                 uint32_t count, uint32_t items, const void *chunks,
+                                 const void *rots, hipStream_t st) {
+    hipLaunchKernelGGL((k_batch_tile_round<T, B, kBatchTileM>), dim3(grid),
+                       dim3(1u << (B - kBatchTileM)), 0, st, passes, first, count, items,
+                       (const ChunkRec<T> *)chunks, rots);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t launch_round(int B, unsigned grid, const BTilePass *ps, const uint32_t *first,
+                               uint32_t count, uint32_t items, const void *chunks,
+                               const void *rots, hipStream_t st) {
+    if constexpr (sizeof(T) == 4) {
+        if (B == 14) return launch_round_b<T, 14>(grid, ps, first, count, items, chunks, rots, st);
+        if (B == 13) return launch_round_b<T, 13>(grid, ps, first, count, items, chunks, rots, st);
+    } else {
+        if (B == 11) return launch_round_b<T, 11>(grid, ps, first, count, items, chunks, rots, st);
+    }
+    if (B == 12) return launch_round_b<T, 12>(grid, ps, first, count, items, chunks, rots, st);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace prx
 
 extern "C" {
 
@@ -300,51 +403,64 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
         const size_t rsz = dtype == PRX_C64 ? sizeof(RotRec<float>) : sizeof(RotRec<double>);
         const size_t csz = dtype == PRX_C64 ? sizeof(ChunkRec<float>) : sizeof(ChunkRec<double>);
         const int TB = batch_tile_qubits(dtype);
-        PlanCfg span_cfg;
-        span_cfg.span_only = true;
-        span_cfg.pad_rank = kBatchRank;
-        span_cfg.span_m = kBatchRank;
-        span_cfg.renorm_every = -1;
-        span_cfg.max_fuse = 64;
+        const int nres = resident_max_qubits(dtype);
+        PlanCfg res_cfg;
+        res_cfg.resident = true;
+        res_cfg.m = kBatchTileM;
+        res_cfg.renorm_every = -1;
+        res_cfg.max_fuse = 128;
+        res_cfg.commuting = true;
         PlanCfg tile_cfg;
         tile_cfg.tile_only = true;
-        tile_cfg.B = TB;
         tile_cfg.m = kBatchTileM;
         tile_cfg.renorm_every = -1;
         tile_cfg.max_fuse = 128;
-        tile_cfg.max_virtual = kBatchMaxVirtual;
         // exact reorders: a later rotation that fits the pass's frame and
         // commutes with every rotation it passes joins the pass (10-20 %
         // fewer passes on random-order qDRIFT sequences)
         tile_cfg.commuting = true;
+        double amps = 0.0;
+        for (size_t s = 0; s < S; ++s)
+            if (n[s] > nres) amps += std::ldexp(1.0, n[s]);
+        b->B = batch_frame_qubits(dtype, amps);
+        b->info.samples = S;
+        std::vector<TileSample> tiles;
         for (size_t s = 0; s < S; ++s) {
-            const bool tile = n[s] >= TB;
+            const bool resident = n[s] <= nres;
+            b->samples.push_back(BSample{0, basis_idx[s]});
+            size_t passes = 0;
             prx_plan *P = nullptr;
-            prx_status st = plan_create_cfg(sched[s], n[s], dtype, tile ? tile_cfg : span_cfg, &P);
-            if (st != PRX_OK) {
-                delete b;
-                return st;
+            if (n[s] >= TB) ++b->info.tile_samples;
+            if (n[s] >= TB && n[s] <= 14) {
+                // samples up to two qubits above the tile size report the
+                // passes of narrow frames, whatever they run
+                tile_cfg.narrow = true;
+                tile_cfg.B = TB;
+                tile_cfg.max_virtual = TB - kMinTileLow;
+                prx_status st = plan_create_cfg(sched[s], n[s], dtype, tile_cfg, &P);
+                if (st != PRX_OK) {
+                    delete b;
+                    return st;
+                }
+                passes = P->passes.size();
+                prx_plan_destroy(P);
             }
-            // every sample keeps a BSample (state address and overlap index);
-            // a tile-mode sample has no span passes
-            BSample sm;
-            std::memset(&sm, 0, sizeof(sm));
-            sm.n = (uint32_t)n[s];
-            sm.ncos = 1ull << (n[s] - kBatchRank);
-            sm.Q = (uint32_t)((sm.ncos + kSliceCosets - 1) / kSliceCosets);
-            sm.basis_idx = basis_idx[s];
-            sm.pass_begin = (uint32_t)b->passes.size();
-            const uint32_t rot_base = (uint32_t)(b->rots.size() / rsz);
-            if (tile) {
-                BTSample ts;
-                std::memset(&ts, 0, sizeof(ts));
-                ts.n = (uint32_t)n[s];
-                ts.nsets = (uint32_t)(1ull << (n[s] - TB));
-                ts.pass_begin = (uint32_t)b->tpasses.size();
-                ts.pass_count = (uint32_t)P->passes.size();
-                const uint32_t chunk_base = (uint32_t)(b->tchunks.size() / csz);
+            if (!resident) {
+                tile_cfg.narrow = false;
+                tile_cfg.B = b->B;
+                tile_cfg.max_virtual = b->B - kMinTileLow;
+                prx_status st = plan_create_cfg(sched[s], n[s], dtype, tile_cfg, &P);
+                if (st != PRX_OK) {
+                    delete b;
+                    return st;
+                }
+                if (n[s] > 14) passes = P->passes.size();
+                TileSample ts;
+                ts.sample = (uint32_t)s;
+                ts.nsets = (uint32_t)(1ull << (n[s] - b->B));
+                const uint32_t chunk_base = append_tables(b, P, csz, rsz);
                 for (const Pass &ps : P->passes) {
-                    if (ps.kind != kTile || ps.B != TB || ps.m != kBatchTileM) {
+                    if (ps.kind != kTile || ps.B != b->B || ps.m != kBatchTileM) {
                         prx_plan_destroy(P);
                         delete b;
                         return fail(PRX_ERR_UNSUPPORTED, "tile-only plan with another pass kind");
@@ -352,79 +468,44 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
                     TileArgs ta;
                     tile_args(n[s], dtype, ps, ta);
                     ta.chunk_begin += chunk_base;
-                    b->tpasses.push_back(ta);
+                    ts.passes.push_back(ta);
+                    ts.rots.push_back((uint32_t)(ps.r1 - ps.r0));
                 }
-                const size_t at = b->tchunks.size();
-                b->tchunks.insert(b->tchunks.end(), P->chunk_table.begin(), P->chunk_table.end());
-                for (size_t c = at; c < b->tchunks.size(); c += csz)
-                    reinterpret_cast<ChunkHead *>(b->tchunks.data() + c)->rot_begin += rot_base;
-                b->tsamples.push_back(ts);
-            } else {
-                sm.pass_count = (uint32_t)P->passes.size();
-                for (const Pass &ps : P->passes) {
-                    BPass bp;
-                    std::memset(&bp, 0, sizeof(bp));
-                    for (int i = 0; i < kBatchRank; ++i) {
-                        bp.basis[i] = ps.basis[i];
-                        bp.pivot[i] = ps.pivot[i];
-                    }
-                    bp.rot_begin = rot_base + (uint32_t)ps.r0;
-                    bp.rot_count = (uint32_t)(ps.r1 - ps.r0);
-                    bp.scale = ps.scale;
-                    for (int i = 0; i < kBatchRank; ++i) bp.fscale[i] = ps.fscale[i];
-                    b->passes.push_back(bp);
-                }
+                tiles.push_back(std::move(ts));
+                prx_plan_destroy(P);
             }
-            b->rots.insert(b->rots.end(), P->rot_table.begin(), P->rot_table.end());
-            b->samples.push_back(sm);
-            if (tile) b->tsrc.push_back((uint32_t)s);
-            prx_plan_destroy(P);
+            if (resident) {
+                res_cfg.B = n[s];
+                prx_status st = plan_create_cfg(sched[s], n[s], dtype, res_cfg, &P);
+                if (st != PRX_OK) {
+                    delete b;
+                    return st;
+                }
+                if (n[s] < TB) passes = P->passes.size();
+                if (!P->chunks.empty()) {
+                    BResident r;
+                    std::memset(&r, 0, sizeof(r));
+                    r.n = (uint32_t)n[s];
+                    r.chunk_count = (uint32_t)P->chunks.size();
+                    r.chunk_begin = append_tables(b, P, csz, rsz);
+                    b->residents.push_back(r);
+                    b->rsrc.push_back((uint32_t)s);
+                }
+                prx_plan_destroy(P);
+            }
+            b->info.passes += passes;
+            b->info.rounds = std::max(b->info.rounds, passes);
+            b->info.amp_sweeps += (double)passes * std::ldexp(1.0, n[s]);
         }
-        // samples sorted by pass count (descending): round p's active samples
-        // are a prefix of this order (tile-mode samples sort last with no
-        // span passes)
-        b->order.resize(S);
-        for (size_t s = 0; s < S; ++s) b->order[s] = (uint32_t)s;
-        std::stable_sort(b->order.begin(), b->order.end(), [&](uint32_t x, uint32_t y) {
-            return b->samples[x].pass_count > b->samples[y].pass_count;
-        });
-        b->prefixQ.assign(S + 1, 0);
-        for (size_t k = 0; k < S; ++k)
-            b->prefixQ[k + 1] = b->prefixQ[k] + b->samples[b->order[k]].Q;
-        const size_t St = b->tsamples.size();
-        b->torder.resize(St);
-        for (size_t s = 0; s < St; ++s) b->torder[s] = (uint32_t)s;
-        std::stable_sort(b->torder.begin(), b->torder.end(), [&](uint32_t x, uint32_t y) {
-            return b->tsamples[x].pass_count > b->tsamples[y].pass_count;
-        });
-        b->tprefix.assign(St + 1, 0);
-        for (size_t k = 0; k < St; ++k)
-            b->tprefix[k + 1] = b->tprefix[k] + b->tsamples[b->torder[k]].nsets;
-        const uint32_t span_rounds = b->samples[b->order[0]].pass_count;
-        const uint32_t tile_rounds = St ? b->tsamples[b->torder[0]].pass_count : 0;
-        b->rounds = std::max(span_rounds, tile_rounds);
-        b->round_active.assign(b->rounds, 0);
-        b->tround_active.assign(b->rounds, 0);
-        size_t active = S, tactive = St;
-        for (uint32_t p = 0; p < b->rounds; ++p) {
-            while (active > 0 && b->samples[b->order[active - 1]].pass_count <= p) --active;
-            while (tactive > 0 && b->tsamples[b->torder[tactive - 1]].pass_count <= p) --tactive;
-            b->round_active[p] = (uint32_t)active;
-            b->tround_active[p] = (uint32_t)tactive;
-            b->total_items += b->prefixQ[active];
-            b->total_tile_items += b->tprefix[tactive];
-        }
+        make_launches(b);
+        make_rounds(b, tiles);
         size_t o = 0;
-        b->off_samples = o;  o = al256(o + S * sizeof(BSample));
-        b->off_passes = o;   o = al256(o + b->passes.size() * sizeof(BPass));
-        b->off_rots = o;     o = al256(o + b->rots.size() + kRecordReadAhead);
-        b->off_prefix = o;   o = al256(o + b->prefixQ.size() * sizeof(uint64_t));
-        b->off_order = o;    o = al256(o + S * sizeof(uint32_t));
-        b->off_tsamples = o; o = al256(o + St * sizeof(BTSample));
-        b->off_tpasses = o;  o = al256(o + b->tpasses.size() * sizeof(TileArgs));
-        b->off_tchunks = o;  o = al256(o + b->tchunks.size());
-        b->off_tprefix = o;  o = al256(o + b->tprefix.size() * sizeof(uint64_t));
-        b->off_torder = o;   o = al256(o + St * sizeof(uint32_t));
+        b->off_samples = o;   o = al256(o + S * sizeof(BSample));
+        b->off_residents = o; o = al256(o + b->residents.size() * sizeof(BResident));
+        b->off_tpasses = o;   o = al256(o + b->tpasses.size() * sizeof(BTilePass));
+        b->off_tfirst = o;    o = al256(o + b->tfirst.size() * sizeof(uint32_t));
+        b->off_chunks = o;    o = al256(o + b->chunks.size());
+        b->off_rots = o;      o = al256(o + b->rots.size() + kRecordReadAhead);
         b->total = o;
     } catch (const std::bad_alloc &) {
         delete b;
@@ -438,18 +519,7 @@ size_t prx_batch_workspace_bytes(const prx_batch *b) { return b ? b->total : 0; 
 
 prx_status prx_batch_get_info(const prx_batch *b, prx_batch_info *out) {
     if (!b || !out) return fail(PRX_ERR_INVALID, "null pointer");
-    std::memset(out, 0, sizeof(*out));
-    out->samples = b->S;
-    out->tile_samples = b->tsamples.size();
-    out->rounds = b->rounds;
-    for (const BSample &s : b->samples) {
-        out->passes += s.pass_count;
-        out->amp_sweeps += (double)s.pass_count * std::ldexp(1.0, (int)s.n);
-    }
-    for (const BTSample &s : b->tsamples) {
-        out->passes += s.pass_count;
-        out->amp_sweeps += (double)s.pass_count * std::ldexp(1.0, (int)s.n);
-    }
+    *out = b->info;
     return PRX_OK;
 }
 
@@ -463,34 +533,26 @@ prx_status prx_batch_upload(prx_batch *b, void *const *psi, void *ws, size_t ws_
             return fail(PRX_ERR_INVALID, "null or misaligned state pointer");
         b->samples[s].psi = (uint64_t)(uintptr_t)psi[s];
     }
-    for (size_t t = 0; t < b->tsamples.size(); ++t) b->tsamples[t].psi = b->samples[b->tsrc[t]].psi;
+    for (size_t t = 0; t < b->tpasses.size(); ++t) b->tpasses[t].psi = b->samples[b->tsrc[t]].psi;
+    for (size_t r = 0; r < b->residents.size(); ++r)
+        b->residents[r].psi = b->samples[b->rsrc[r]].psi;
     hipStream_t st = (hipStream_t)stream;
     char *w = (char *)ws;
-    PRX_HIP(hipMemcpyAsync(w + b->off_samples, b->samples.data(), b->S * sizeof(BSample),
-                           hipMemcpyHostToDevice, st));
-    PRX_HIP(hipMemcpyAsync(w + b->off_passes, b->passes.data(), b->passes.size() * sizeof(BPass),
-                           hipMemcpyHostToDevice, st));
-    if (!b->rots.empty())
-        PRX_HIP(hipMemcpyAsync(w + b->off_rots, b->rots.data(), b->rots.size(),
-                               hipMemcpyHostToDevice, st));
-    PRX_HIP(hipMemcpyAsync(w + b->off_prefix, b->prefixQ.data(),
-                           b->prefixQ.size() * sizeof(uint64_t), hipMemcpyHostToDevice, st));
-    PRX_HIP(hipMemcpyAsync(w + b->off_order, b->order.data(), b->S * sizeof(uint32_t),
-                           hipMemcpyHostToDevice, st));
-    const size_t St = b->tsamples.size();
-    if (St) {
-        PRX_HIP(hipMemcpyAsync(w + b->off_tsamples, b->tsamples.data(), St * sizeof(BTSample),
-                               hipMemcpyHostToDevice, st));
-        PRX_HIP(hipMemcpyAsync(w + b->off_tpasses, b->tpasses.data(),
-                               b->tpasses.size() * sizeof(TileArgs), hipMemcpyHostToDevice, st));
-        if (!b->tchunks.empty())
-            PRX_HIP(hipMemcpyAsync(w + b->off_tchunks, b->tchunks.data(),
-                                   b->tchunks.size(), hipMemcpyHostToDevice, st));
-        PRX_HIP(hipMemcpyAsync(w + b->off_tprefix, b->tprefix.data(),
-                               b->tprefix.size() * sizeof(uint64_t), hipMemcpyHostToDevice, st));
-        PRX_HIP(hipMemcpyAsync(w + b->off_torder, b->torder.data(), St * sizeof(uint32_t),
-                               hipMemcpyHostToDevice, st));
-    }
+    const struct {
+        size_t off;
+        const void *src;
+        size_t bytes;
+    } tables[] = {
+        {b->off_samples, b->samples.data(), b->S * sizeof(BSample)},
+        {b->off_residents, b->residents.data(), b->residents.size() * sizeof(BResident)},
+        {b->off_tpasses, b->tpasses.data(), b->tpasses.size() * sizeof(BTilePass)},
+        {b->off_tfirst, b->tfirst.data(), b->tfirst.size() * sizeof(uint32_t)},
+        {b->off_chunks, b->chunks.data(), b->chunks.size()},
+        {b->off_rots, b->rots.data(), b->rots.size()},
+    };
+    for (const auto &t : tables)
+        if (t.bytes)
+            PRX_HIP(hipMemcpyAsync(w + t.off, t.src, t.bytes, hipMemcpyHostToDevice, st));
     PRX_HIP(hipStreamSynchronize(st));
     return PRX_OK;
 }
@@ -501,65 +563,36 @@ prx_status prx_batch_execute(const prx_batch *b, void *ws, size_t ws_bytes,
     if (ws_bytes < b->total) return fail(PRX_ERR_INVALID, "workspace too small");
     hipStream_t st = (hipStream_t)stream;
     char *w = (char *)ws;
-    BatchArgs a;
-    a.samples = (const BSample *)(w + b->off_samples);
-    a.passes = (const BPass *)(w + b->off_passes);
-    a.rots = w + b->off_rots;
-    a.prefixQ = (const uint64_t *)(w + b->off_prefix);
-    a.order = (const uint32_t *)(w + b->off_order);
-    BatchTileArgs ta;
-    ta.samples = (const BTSample *)(w + b->off_tsamples);
-    ta.passes = (const TileArgs *)(w + b->off_tpasses);
-    ta.chunks = w + b->off_tchunks;
-    ta.rots = w + b->off_rots;
-    ta.prefixW = (const uint64_t *)(w + b->off_tprefix);
-    ta.order = (const uint32_t *)(w + b->off_torder);
+    const void *chunks = w + b->off_chunks, *rots = w + b->off_rots;
+    const uint64_t cap = b->max_grid ? b->max_grid : kTileGridCap;
+    const uint64_t tcap = std::min(cap, kTileGridCap);
+    for (const prx_batch::Launch &l : b->launches) {
+        const BResident *r = (const BResident *)(w + b->off_residents) + l.first;
+        const unsigned grid = (unsigned)std::min<uint64_t>(l.count, cap);
+        PRX_HIP(b->dtype == PRX_C64
+                    ? launch_residents<float>(l.B, grid, r, l.count, chunks, rots, st)
+                    : launch_residents<double>(l.B, grid, r, l.count, chunks, rots, st));
+    }
     int dev = 0, cus = 256;
     PRX_HIP(hipGetDevice(&dev));
     PRX_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    uint64_t cap = (uint64_t)std::max(1, cus) * 8u;
-    uint64_t tcap = kTileGridCap;
-    if (b->max_grid) {
-        cap = std::min<uint64_t>(cap, b->max_grid);
-        tcap = std::min<uint64_t>(tcap, b->max_grid);
-    }
-    const unsigned tile_threads = 1u << (batch_tile_qubits(b->dtype) - kBatchTileM);
-    for (uint32_t p = 0; p < b->rounds; ++p) {
-        const uint32_t tactive = b->tround_active[p];
-        const uint64_t titems = b->tprefix[tactive];
-        if (titems) {
-            const unsigned grid = (unsigned)std::min<uint64_t>(titems, tcap);
-            if (b->dtype == PRX_C64)
-                hipLaunchKernelGGL((k_batch_tile_round<float, 12, kBatchTileM>), dim3(grid),
-                                   dim3(tile_threads), 0, st, ta.samples, ta.passes,
-                                   (const ChunkRec<float> *)ta.chunks, ta.rots, ta.prefixW,
-                                   ta.order, p, tactive, titems);
-            else
-                hipLaunchKernelGGL((k_batch_tile_round<double, 11, kBatchTileM>), dim3(grid),
-                                   dim3(tile_threads), 0, st, ta.samples, ta.passes,
-                                   (const ChunkRec<double> *)ta.chunks,
-                                   ta.rots, ta.prefixW, ta.order, p, tactive, titems);
-            PRX_HIP(hipGetLastError());
-        }
-        const uint32_t active = b->round_active[p];
-        const uint64_t items = b->prefixQ[active];
-        if (items) {
-            const unsigned grid = (unsigned)std::min<uint64_t>(items, cap);
-            if (b->dtype == PRX_C64)
-                hipLaunchKernelGGL(k_batch_round<float>, dim3(grid), dim3(256), 0, st, a.samples,
-                                   a.passes, a.rots, a.prefixQ, a.order, p, active, items);
-            else
-                hipLaunchKernelGGL(k_batch_round<double>, dim3(grid), dim3(256), 0, st, a.samples,
-                                   a.passes, a.rots, a.prefixQ, a.order, p, active, items);
-            PRX_HIP(hipGetLastError());
-        }
+    // (128 KiB sets: one resident workgroup per CU)
+    const uint64_t rcap = b->B == 14 ? std::min<uint64_t>(tcap, std::max(1, cus)) : tcap;
+    for (const prx_batch::Round &r : b->rounds) {
+        const BTilePass *ps = (const BTilePass *)(w + b->off_tpasses) + r.begin;
+        const uint32_t *first = (const uint32_t *)(w + b->off_tfirst) + r.begin;
+        const unsigned grid = (unsigned)std::min<uint64_t>(r.items, rcap);
+        PRX_HIP(b->dtype == PRX_C64
+                    ? launch_round<float>(b->B, grid, ps, first, r.count, r.items, chunks, rots, st)
+                    : launch_round<double>(b->B, grid, ps, first, r.count, r.items, chunks, rots, st));
     }
     const unsigned rb = (unsigned)((b->S + 255) / 256);
+    const BSample *samples = (const BSample *)(w + b->off_samples);
     if (b->dtype == PRX_C64)
-        hipLaunchKernelGGL(k_batch_overlaps<float>, dim3(rb), dim3(256), 0, st, a.samples,
+        hipLaunchKernelGGL(k_batch_overlaps<float>, dim3(rb), dim3(256), 0, st, samples,
                            (uint32_t)b->S, overlaps_dev);
     else
-        hipLaunchKernelGGL(k_batch_overlaps<double>, dim3(rb), dim3(256), 0, st, a.samples,
+        hipLaunchKernelGGL(k_batch_overlaps<double>, dim3(rb), dim3(256), 0, st, samples,
                            (uint32_t)b->S, overlaps_dev);
     PRX_HIP(hipGetLastError());
     return PRX_OK;

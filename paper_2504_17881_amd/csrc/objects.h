@@ -74,13 +74,13 @@ struct PlanCfg {
     int max_virtual = 2;
     int renorm_every = 1;
     bool commuting = false;
-    bool span_only = false;  // batched plans: every pass is a span pass ...
-    int pad_rank = 0;        // ... whose basis is padded to exactly this rank
     bool tile_only = false;  // batched plans: every pass is a tile pass
     bool narrow = true;      // at most n - B virtual qubits per frame
     bool relabel = false;    // qubit-relabelling passes between segments
     unsigned grid_cap = (unsigned)kMaxGridBlocks;  // workgroups per sweep launch
     bool shaped = false;     // the caller chose frames or spans: no resident plan
+    bool resident = false;   // batched plans: a resident plan, commuting rotations brought
+                             // forward into a chunk that they fit
 };
 
 // Kernel arguments of a tile pass of a plan for n qubits.

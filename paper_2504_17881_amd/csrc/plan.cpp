@@ -312,13 +312,6 @@ struct Builder {
             basis.push_back(1ull << (P.n - 1));
             g.add(1ull << (P.n - 1));
         }
-        // fixed-rank plans: pad with unused high unit directions
-        for (int q = P.n - 1; (int)basis.size() < cfg.pad_rank && q >= 0; --q) {
-            if (!g.contains(1ull << q)) {
-                g.add(1ull << q);
-                basis.push_back(1ull << q);
-            }
-        }
         Pass ps;
         ps.kind = kSpan;
         ps.r0 = p;
@@ -461,7 +454,32 @@ struct Builder {
     // pass's unscaled amplitudes are built for).
     void run_resident() {
         size_t p = P.begin;
+        if (cfg.commuting) fill_chunks();
         while (p < end) p = emit_tile(p, 0);
+    }
+
+    // With commuting on, a resident plan's only question is how many rotations
+    // a chunk takes: a later rotation whose mask the chunk's basis has, or has
+    // room for, comes forward when it commutes with those it passes.
+    void fill_chunks() {
+        for (size_t j = P.begin; j < end;) {
+            Gf2 g;
+            uint64_t basis[kMaxChunkRank];
+            int m = 0;
+            auto fits = [&](const KRot &r) {
+                return r.x == 0 || std::find(basis, basis + m, r.x) != basis + m ||
+                       (m < cfg.m && !g.contains(r.x));
+            };
+            const size_t first = j;
+            for (; j < end && j - first < (size_t)kMaxChunkRots; ++j) {
+                if (!fits(R[j]) && !pull_forward(j, fits)) break;
+                const uint64_t x = R[j].x;
+                if (x && std::find(basis, basis + m, x) == basis + m) {
+                    g.add(x);
+                    basis[m++] = x;
+                }
+            }
+        }
     }
 
     // Every pass a tile pass (batched tile rounds): from each position the
@@ -482,11 +500,6 @@ struct Builder {
             if (gbest < 0) throw std::runtime_error("tile-only plan: no tile frame fits");
             p = emit_tile(p, gbest);
         }
-    }
-
-    void run_span_only() {
-        size_t p = P.begin;
-        while (p < end) p = emit_span(p);
     }
 
     // Longest pass from p: its end, the kind (kSpan or kTile) and tile g.
@@ -887,6 +900,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             P->cfg.commuting = P->cfg.relabel = false;  // every rotation fits already
         }
         if (!internal) P->cfg.narrow = P->cfg.tile_only;
+        if (internal) P->resident = internal->resident;
         if (P->cfg.tile_only && (!fused || n < P->cfg.B)) {
             delete P;
             return fail(PRX_ERR_INVALID, "tile_only needs a fused kernel and n >= tile_qubits");
@@ -922,7 +936,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         if (P->resident) {
             Builder bld(*P, P->end);
             bld.run_resident();
-            if (resident_loses(*P)) {
+            if (!internal && resident_loses(*P)) {
                 P->resident = false;
                 P->cfg = tiled;
                 P->passes.clear();
@@ -932,7 +946,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
                 recs.swap(bld.recs);
             }
         }
-        const bool relabel = P->cfg.relabel && fused && !P->cfg.span_only &&
+        const bool relabel = P->cfg.relabel && fused &&
                              n >= std::max(P->cfg.B + 2, 14) &&
                              tile_supported(dtype, P->cfg.B, P->cfg.m);
         if (P->resident) {
@@ -940,9 +954,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         } else if (!relabel) {
             Builder bld(*P, P->end);
             // span passes need 2^(n - m) >= 1 cosets; tiny states fall back to plain
-            if (P->cfg.span_only)
-                bld.run_span_only();
-            else if (P->cfg.tile_only)
+            if (P->cfg.tile_only)
                 bld.run_tile_only();
             else if (!fused || n < 4)
                 bld.run_plain();
