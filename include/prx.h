@@ -362,7 +362,7 @@ typedef struct prx_graph prx_graph;
  * A sample of up to 14 qubits (13 for complex128) stays in one workgroup's
  * LDS for its whole sequence; all such samples share one launch (one per size
  * when there are more than 256).  A larger one is segmented into tile passes
- * of 12 to 14 tile qubits (11 or 12 for complex128), by the amplitudes of the
+ * of 12 to 14 tile qubits (11 or 12 for complex128), by the sizes in the
  * batch.  Both bring a later rotation forward when it commutes with every
  * rotation it passes (the product is unchanged; only the rounding order
  * differs).  Round p applies pass p of every larger sample that has one, as

@@ -31,15 +31,18 @@ static constexpr uint64_t kTileGridCap = 1u << 20;
 // More are launched by size, so that small ones share a CU.
 static constexpr size_t kResidentOneLaunch = 256;
 static int batch_tile_qubits(prx_dtype dt) { return dt == PRX_C64 ? 12 : 11; }
-// Tile qubits of a batch's rounds by the amplitudes of a round with every
-// tile sample.  Larger frames make fewer sweeps (32 samples of 16 to 22
-// qubits: 2485, 2121, 1805 passes with 12, 13, 14 qubits), smaller ones leave
-// more workgroups on a CU to overlap and shorter ends of rounds.  Measured
-// (us per batch): 8 samples of 24 qubits 29201 / 26586 / 24617, 12 of 20 to 23
-// 9338 / 9152 / 9431, 64 of 15 to 18 2644 / 2602 / 2682; complex128, 32 of 15
-// to 21, 10773 with 11 qubits, 9539 with 12, 10444 with 13.
-static int batch_frame_qubits(prx_dtype dt, double amps) {
-    if (dt == PRX_C64) return amps >= 0x1p26 ? 14 : amps >= 0x1p23 ? 13 : 12;
+// Tile qubits of a batch's rounds, by the amplitudes of its tile samples and
+// the fewest qubits among them.  Larger frames make fewer sweeps (32 samples
+// of 16 to 22 qubits: 2485, 2121, 1805 passes with 12, 13, 14 qubits), smaller
+// ones leave more workgroups on a CU to overlap and shorter ends of rounds.
+// Measured (us per batch, 12 / 13 / 14 qubits): 20 samples of 17 qubits 472 /
+// 491 / 636, 20 of 19 1280 / 1182 / 1248, 24 of 23 21456 / 19488 / 20786, 6 of
+// 24 6448 / 5845 / 5479, 4 of 25 8212 / 7609 / 7289; 24 samples of 22 qubits,
+// one 14-qubit set of each per CU, take 12311 with 14 and 8847 with 13.
+// complex128, 32 of 15 to 21: 10773 with 11 qubits, 9539 with 12, 10444 with
+// 13; 64 of 14 to 17 3096 with 11 and 2736 with 12.
+static int batch_frame_qubits(prx_dtype dt, double amps, int fewest) {
+    if (dt == PRX_C64) return fewest >= 24 ? 14 : amps >= 0x1p23 ? 13 : 12;
     return amps >= 0x1p19 ? 12 : 11;
 }
 
@@ -420,9 +423,13 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
         // fewer passes on random-order qDRIFT sequences)
         tile_cfg.commuting = true;
         double amps = 0.0;
+        int fewest = 64;
         for (size_t s = 0; s < S; ++s)
-            if (n[s] > nres) amps += std::ldexp(1.0, n[s]);
-        b->B = batch_frame_qubits(dtype, amps);
+            if (n[s] > nres) {
+                amps += std::ldexp(1.0, n[s]);
+                fewest = std::min(fewest, n[s]);
+            }
+        b->B = batch_frame_qubits(dtype, amps, fewest);
         b->info.samples = S;
         std::vector<TileSample> tiles;
         for (size_t s = 0; s < S; ++s) {

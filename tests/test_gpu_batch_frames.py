@@ -64,8 +64,8 @@ def test_more_residents_than_one_launch(dtype, max_grid):
 @pytest.mark.parametrize("dtype,ns,max_grid", [
     (P.PRX_C64, [15, 14, 17, 15], 0),           # 12-qubit frames
     (P.PRX_C64, [22, 15, 21, 9, 22], 0),        # 13
-    (P.PRX_C64, [25, 15, 24, 25, 13], 0),       # 14: resident workgroups, 4098 items over 256
-    (P.PRX_C64, [26, 15], 5),
+    (P.PRX_C64, [24, 25, 13, 24], 0),           # 14: 4096 items over the resident workgroups
+    (P.PRX_C64, [24, 24], 5),
     (P.PRX_C128, [14, 15, 13, 14], 0),          # 11
     (P.PRX_C128, [19, 14, 18, 8], 0),           # 12
     (P.PRX_C128, [19, 14, 18], 3),
