@@ -247,13 +247,14 @@ unsigned plain_blocks(int n, bool diag, unsigned cap);
 bool span_supported(prx_dtype dt, int m);
 bool tile_supported(prx_dtype dt, int B, int m);
 
-// Reductions.  `ws` holds kReduceBlocks * 2 doubles of partials plus 4
-// doubles of result.
+// Reductions.  `part` holds kReduceBlocks * 2 doubles of partials; `out` (2
+// doubles) is memory that the device writes: a workspace or a host slot.
 static constexpr unsigned kReduceBlocks = 1024;
-hipError_t launch_overlap(prx_dtype dt, const void *psi0, const void *psi, int n, double *ws,
-                          hipStream_t s);
-hipError_t launch_norm2(prx_dtype dt, const void *psi, int n, double *ws, hipStream_t s);
-hipError_t launch_scale(prx_dtype dt, void *psi, int n, const double *scale_dev,
+static constexpr unsigned kReduceThreads = 512;
+hipError_t launch_overlap(prx_dtype dt, const void *psi0, const void *psi, int n, double *part,
+                          double *out, hipStream_t s);
+hipError_t launch_norm2(prx_dtype dt, const void *psi, int n, double *part, double *out,
                         hipStream_t s);
+hipError_t launch_scale(prx_dtype dt, void *psi, int n, double scale, hipStream_t s);
 
 }  // namespace prx

@@ -415,6 +415,125 @@ __global__ void __launch_bounds__(256) k_permute(Cx<T> *__restrict__ psi, PermAr
 
 // ------------------------------------------------------------ reductions
 
+// Compensated accumulator: every addition's rounding error, exact in FP64
+// (Knuth's two-sum, no comparison), is summed beside the sum.
+struct Comp {
+    double s = 0.0, c = 0.0;
+    __device__ __forceinline__ void add(double v) {
+        const double t = s + v, w = t - s;
+        c += (s - (t - w)) + (v - w);
+        s = t;
+    }
+    __device__ __forceinline__ void add(const Comp &o) {
+        add(o.s);
+        c += o.c;
+    }
+    __device__ __forceinline__ double value() const { return s + c; }
+};
+
+// Fixed-shape sum over a block of NT threads (deterministic for a fixed launch
+// shape); the result is in thread 0.
+template <int NT>
+__device__ __forceinline__ Comp block_comp(Comp v, double *red) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        Comp o;
+        o.s = __shfl_down(v.s, off, 64);
+        o.c = __shfl_down(v.c, off, 64);
+        v.add(o);
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __syncthreads();  // `red` may hold the sum before this one
+    if (lane == 0) {
+        red[2 * wave] = v.s;
+        red[2 * wave + 1] = v.c;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < NT / 64; ++i) {
+            Comp o;
+            o.s = red[2 * i];
+            o.c = red[2 * i + 1];
+            v.add(o);
+        }
+    }
+    return v;
+}
+
+// The overlap's and the norm's first stage: 16 bytes per lane and load, U loads
+// of every operand in flight, bound by the read bandwidth.  Block b leaves its
+// sum at part[2b], or, when it is the only block, the result at out.
+template <typename T, bool NORM>
+__global__ void __launch_bounds__(kReduceThreads)
+    k_reduce(const Cx<T> *__restrict__ a, const Cx<T> *__restrict__ b, uint64_t ngroups,
+             double *__restrict__ part, double *__restrict__ out) {
+    constexpr int G = Group<T>::G, U = 4;
+    typedef typename Group<T>::V V;
+    __shared__ double red[2 * kReduceThreads / 64];
+    Comp re, im;
+    auto take = [&](const V &u, const V &v) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const double ur = u[2 * i], ui = u[2 * i + 1];
+            if constexpr (NORM) {
+                re.add(ur * ur);
+                re.add(ui * ui);
+            } else {  // conj(u) * v
+                const double vr = v[2 * i], vi = v[2 * i + 1];
+                re.add(ur * vr);
+                re.add(ui * vi);
+                im.add(ur * vi);
+                im.add(-ui * vr);
+            }
+        }
+    };
+    const V *pa = reinterpret_cast<const V *>(a), *pb = reinterpret_cast<const V *>(b);
+    const uint64_t stride = (uint64_t)gridDim.x * kReduceThreads;
+    uint64_t k = (uint64_t)blockIdx.x * kReduceThreads + threadIdx.x;
+    for (; k + (U - 1) * stride < ngroups; k += U * stride) {
+        V u[U], v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            u[i] = __builtin_nontemporal_load(pa + k + i * stride);
+            if constexpr (!NORM) v[i] = __builtin_nontemporal_load(pb + k + i * stride);
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i) take(u[i], v[i]);
+    }
+    for (; k < ngroups; k += stride) {
+        const V u = pa[k];
+        if constexpr (NORM)
+            take(u, u);
+        else
+            take(u, pb[k]);
+    }
+    re = block_comp<kReduceThreads>(re, red);
+    if constexpr (!NORM) im = block_comp<kReduceThreads>(im, red);
+    if (threadIdx.x == 0) {
+        double *o = gridDim.x == 1 ? out : part + 2 * blockIdx.x;
+        o[0] = re.value();
+        o[1] = im.value();
+    }
+}
+
+// Sums `count` <= 1024 (re, im) partials into out[0..1].
+__global__ void __launch_bounds__(1024) k_finish_pairs(const double *__restrict__ part,
+                                                       unsigned count, double *__restrict__ out) {
+    static_assert(kReduceBlocks <= 1024, "one partial per thread");
+    __shared__ double red[32];
+    Comp re, im;
+    if (threadIdx.x < count) {
+        re.s = part[2 * threadIdx.x];
+        im.s = part[2 * threadIdx.x + 1];
+    }
+    re = block_comp<1024>(re, red);
+    im = block_comp<1024>(im, red);
+    if (threadIdx.x == 0) {
+        out[0] = re.value();
+        out[1] = im.value();
+    }
+}
+
 // Fixed-shape tree over the block (deterministic for a fixed launch shape).
 __device__ __forceinline__ double tree256(double v, double *sh) {
     sh[threadIdx.x] = v;
@@ -426,64 +545,6 @@ __device__ __forceinline__ double tree256(double v, double *sh) {
     const double r = sh[0];
     __syncthreads();
     return r;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_overlap(const Cx<T> *__restrict__ a,
-                                                 const Cx<T> *__restrict__ b, uint64_t N,
-                                                 double *__restrict__ part) {
-    __shared__ double sh[256];
-    Neu re, im;
-    const uint64_t stride = (uint64_t)gridDim.x * 256u;
-    for (uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x; k < N; k += stride) {
-        const Cx<T> u = a[k], v = b[k];
-        // conj(u) * v
-        re.add((double)u.re * (double)v.re);
-        re.add((double)u.im * (double)v.im);
-        im.add((double)u.re * (double)v.im);
-        im.add(-(double)u.im * (double)v.re);
-    }
-    const double r = tree256(re.value(), sh);
-    const double i = tree256(im.value(), sh);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = r;
-        part[2 * blockIdx.x + 1] = i;
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(256) k_norm2(const Cx<T> *__restrict__ a, uint64_t N,
-                                               double *__restrict__ part) {
-    __shared__ double sh[256];
-    Neu acc;
-    const uint64_t stride = (uint64_t)gridDim.x * 256u;
-    for (uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x; k < N; k += stride) {
-        const Cx<T> u = a[k];
-        acc.add((double)u.re * (double)u.re);
-        acc.add((double)u.im * (double)u.im);
-    }
-    const double r = tree256(acc.value(), sh);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = r;
-        part[2 * blockIdx.x + 1] = 0.0;
-    }
-}
-
-// Sums `count` (re, im) partials into out[0..1] with one 256-thread block.
-__global__ void __launch_bounds__(256) k_finish_pairs(const double *__restrict__ part,
-                                                      unsigned count, double *__restrict__ out) {
-    __shared__ double sh[256];
-    Neu re, im;
-    for (unsigned i = threadIdx.x; i < count; i += 256u) {
-        re.add(part[2 * i]);
-        im.add(part[2 * i + 1]);
-    }
-    const double r = tree256(re.value(), sh);
-    const double m = tree256(im.value(), sh);
-    if (threadIdx.x == 0) {
-        out[0] = r;
-        out[1] = m;
-    }
 }
 
 // Norm hand-off, stage 1: block b sums its contiguous share of the
@@ -512,16 +573,12 @@ __global__ void __launch_bounds__(1024) k_renorm_finish(const double *__restrict
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_scale(Cx<T> *__restrict__ a, uint64_t N,
-                                               const double *__restrict__ scale) {
-    const T s = (T)scale[0];
+__global__ void __launch_bounds__(256) k_scale(Cx<T> *__restrict__ a, uint64_t ngroups, T s) {
+    typedef typename Group<T>::V V;
+    V *p = reinterpret_cast<V *>(a);
     const uint64_t stride = (uint64_t)gridDim.x * 256u;
-    for (uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x; k < N; k += stride) {
-        Cx<T> u = a[k];
-        u.re *= s;
-        u.im *= s;
-        a[k] = u;
-    }
+    for (uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x; k < ngroups; k += stride)
+        p[k] = p[k] * s;
 }
 
 // ------------------------------------------------------------- launchers
@@ -752,47 +809,45 @@ hipError_t launch_resident(prx_dtype dt, void *psi, int n, const void *rots, con
                : resident_t<double>(psi, n, rots, chunks, chunk_begin, chunk_count, rin, rout, s);
 }
 
-static unsigned reduce_grid(uint64_t N) {
-    const uint64_t want = (N + 256u * 8u - 1) / (256u * 8u);
-    return (unsigned)(want < kReduceBlocks ? (want ? want : 1) : kReduceBlocks);
-}
-
-hipError_t launch_overlap(prx_dtype dt, const void *psi0, const void *psi, int n, double *ws,
-                          hipStream_t s) {
-    const uint64_t N = 1ull << n;
-    const unsigned g = reduce_grid(N);
-    if (dt == PRX_C64)
-        hipLaunchKernelGGL(k_overlap<float>, dim3(g), dim3(256), 0, s, (const Cx<float> *)psi0,
-                           (const Cx<float> *)psi, N, ws);
-    else
-        hipLaunchKernelGGL(k_overlap<double>, dim3(g), dim3(256), 0, s, (const Cx<double> *)psi0,
-                           (const Cx<double> *)psi, N, ws);
-    hipLaunchKernelGGL(k_finish_pairs, dim3(1), dim3(256), 0, s, ws, g, ws + 2 * kReduceBlocks);
+template <typename T, bool NORM>
+static hipError_t reduce_t(const void *a, const void *b, int n, double *part, double *out,
+                           hipStream_t s) {
+    const uint64_t ngroups = (1ull << n) / Group<T>::G;
+    // one block up to 2^13 amplitudes (no second launch), else blocks of eight
+    // groups per thread up to kReduceBlocks
+    const unsigned g =
+        n <= 13 ? 1u
+                : (unsigned)std::min<uint64_t>(kReduceBlocks, (ngroups + kReduceThreads * 8u - 1) /
+                                                                  (kReduceThreads * 8u));
+    hipLaunchKernelGGL((k_reduce<T, NORM>), dim3(g), dim3(kReduceThreads), 0, s, (const Cx<T> *)a,
+                       (const Cx<T> *)b, ngroups, part, out);
+    if (g > 1)
+        hipLaunchKernelGGL(k_finish_pairs, dim3(1), dim3(1024), 0, s, part, g, out);
     return hipGetLastError();
 }
 
-hipError_t launch_norm2(prx_dtype dt, const void *psi, int n, double *ws, hipStream_t s) {
-    const uint64_t N = 1ull << n;
-    const unsigned g = reduce_grid(N);
-    if (dt == PRX_C64)
-        hipLaunchKernelGGL(k_norm2<float>, dim3(g), dim3(256), 0, s, (const Cx<float> *)psi, N, ws);
-    else
-        hipLaunchKernelGGL(k_norm2<double>, dim3(g), dim3(256), 0, s, (const Cx<double> *)psi, N,
-                           ws);
-    hipLaunchKernelGGL(k_finish_pairs, dim3(1), dim3(256), 0, s, ws, g, ws + 2 * kReduceBlocks);
-    return hipGetLastError();
+hipError_t launch_overlap(prx_dtype dt, const void *psi0, const void *psi, int n, double *part,
+                          double *out, hipStream_t s) {
+    return dt == PRX_C64 ? reduce_t<float, false>(psi0, psi, n, part, out, s)
+                         : reduce_t<double, false>(psi0, psi, n, part, out, s);
 }
 
-hipError_t launch_scale(prx_dtype dt, void *psi, int n, const double *scale_dev,
+hipError_t launch_norm2(prx_dtype dt, const void *psi, int n, double *part, double *out,
                         hipStream_t s) {
-    const uint64_t N = 1ull << n;
-    const unsigned g = (unsigned)std::min<uint64_t>((N + 255) / 256, 256u * 64u);
-    if (dt == PRX_C64)
-        hipLaunchKernelGGL(k_scale<float>, dim3(g), dim3(256), 0, s, (Cx<float> *)psi, N, scale_dev);
-    else
-        hipLaunchKernelGGL(k_scale<double>, dim3(g), dim3(256), 0, s, (Cx<double> *)psi, N,
-                           scale_dev);
+    return dt == PRX_C64 ? reduce_t<float, true>(psi, psi, n, part, out, s)
+                         : reduce_t<double, true>(psi, psi, n, part, out, s);
+}
+
+template <typename T>
+static hipError_t scale_t(void *psi, int n, double scale, hipStream_t s) {
+    const uint64_t ngroups = (1ull << n) / Group<T>::G;
+    const unsigned g = (unsigned)std::min<uint64_t>((ngroups + 255) / 256, 256u * 64u);
+    hipLaunchKernelGGL(k_scale<T>, dim3(g), dim3(256), 0, s, (Cx<T> *)psi, ngroups, (T)scale);
     return hipGetLastError();
+}
+
+hipError_t launch_scale(prx_dtype dt, void *psi, int n, double scale, hipStream_t s) {
+    return dt == PRX_C64 ? scale_t<float>(psi, n, scale, s) : scale_t<double>(psi, n, scale, s);
 }
 
 }  // namespace prx
