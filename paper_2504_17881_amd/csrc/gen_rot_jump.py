@@ -143,7 +143,9 @@ def loop_block():
         lines += (["s_load_dwordx8 s[80:87], s[76:77], 0x0"] + fmas(var, "%[ga]", "%[gb]") +
                   ["s_cmp_eq_u32 s78, 0", "s_cbranch_scc1 9f", "s_waitcnt lgkmcnt(0)"] +
                   _dispatch("(2b - 1b)", "-1"))
-    lines += ["9:", "s_mov_b32 %[plo], s76", "s_mov_b32 %[phi], s77", "s_mov_b32 %[cnt], s78"]
+    # (the record loaded ahead is still on its way when the count ends the run)
+    lines += ["9:", "s_waitcnt lgkmcnt(0)",
+              "s_mov_b32 %[plo], s76", "s_mov_b32 %[phi], s77", "s_mov_b32 %[cnt], s78"]
     return lines
 
 
@@ -189,7 +191,9 @@ def loop_block64():
         lines += (loads + fmas(var, "%[ga]", "%[gb]", "v_fma_f64") +
                   ["s_cmp_eq_u32 s78, 0", "s_cbranch_scc1 9f", "s_waitcnt lgkmcnt(0)"] +
                   _dispatch64("(2b - 1b)", "-1"))
-    lines += ["9:", "s_mov_b32 %[plo], s76", "s_mov_b32 %[phi], s77", "s_mov_b32 %[cnt], s78"]
+    # (the record loaded ahead is still on its way when the count ends the run)
+    lines += ["9:", "s_waitcnt lgkmcnt(0)",
+              "s_mov_b32 %[plo], s76", "s_mov_b32 %[phi], s77", "s_mov_b32 %[cnt], s78"]
     return lines
 
 
