@@ -363,6 +363,94 @@ __device__ __forceinline__ void rot_loop(Cx<double> (&amp)[16], uint32_t k0, uin
     cnt = __builtin_amdgcn_readfirstlane(cnt);
 }
 
+// The loops of resident states (rot_lean_*.inc): the same contract without a
+// base tile.
+#include "rot_lean_f32m4.inc"
+__device__ __forceinline__ void rot_lean(Cx<float> (&amp)[16], uint32_t k0, uint32_t &plo,
+                                         uint32_t &phi, uint32_t &cnt) {
+    uint32_t ga, gb;
+    asm volatile(PRX_ROT_LEAN_F32M4
+        : "+v"(amp[0].re), "+v"(amp[0].im), "+v"(amp[1].re), "+v"(amp[1].im),
+          "+v"(amp[2].re), "+v"(amp[2].im), "+v"(amp[3].re), "+v"(amp[3].im),
+          "+v"(amp[4].re), "+v"(amp[4].im), "+v"(amp[5].re), "+v"(amp[5].im),
+          "+v"(amp[6].re), "+v"(amp[6].im), "+v"(amp[7].re), "+v"(amp[7].im),
+          "+v"(amp[8].re), "+v"(amp[8].im), "+v"(amp[9].re), "+v"(amp[9].im),
+          "+v"(amp[10].re), "+v"(amp[10].im), "+v"(amp[11].re), "+v"(amp[11].im),
+          "+v"(amp[12].re), "+v"(amp[12].im), "+v"(amp[13].re), "+v"(amp[13].im),
+          "+v"(amp[14].re), "+v"(amp[14].im), "+v"(amp[15].re), "+v"(amp[15].im),
+          "+{s76}"(plo), "+{s77}"(phi), "+{s78}"(cnt), [ga] "=&v"(ga), [gb] "=&v"(gb)
+        : [k0] "v"(k0)
+        : "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87",
+          "s92", "s93", "s94", "s95", "scc", "memory");
+    plo = __builtin_amdgcn_readfirstlane(plo);
+    phi = __builtin_amdgcn_readfirstlane(phi);
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+}
+#include "rot_lean_f64m4.inc"
+__device__ __forceinline__ void rot_lean(Cx<double> (&amp)[16], uint32_t k0, uint32_t &plo,
+                                         uint32_t &phi, uint32_t &cnt) {
+    asm volatile(PRX_ROT_LEAN_F64M4
+        : "+v"(amp[0].re), "+v"(amp[0].im), "+v"(amp[1].re), "+v"(amp[1].im),
+          "+v"(amp[2].re), "+v"(amp[2].im), "+v"(amp[3].re), "+v"(amp[3].im),
+          "+v"(amp[4].re), "+v"(amp[4].im), "+v"(amp[5].re), "+v"(amp[5].im),
+          "+v"(amp[6].re), "+v"(amp[6].im), "+v"(amp[7].re), "+v"(amp[7].im),
+          "+v"(amp[8].re), "+v"(amp[8].im), "+v"(amp[9].re), "+v"(amp[9].im),
+          "+v"(amp[10].re), "+v"(amp[10].im), "+v"(amp[11].re), "+v"(amp[11].im),
+          "+v"(amp[12].re), "+v"(amp[12].im), "+v"(amp[13].re), "+v"(amp[13].im),
+          "+v"(amp[14].re), "+v"(amp[14].im), "+v"(amp[15].re), "+v"(amp[15].im),
+          "+{s76}"(plo), "+{s77}"(phi), "+{s78}"(cnt)
+        : [k0] "v"(k0)
+        : "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87",
+          "s88", "s89", "s92", "s93", "s94", "s95", "v4", "v5", "v6", "v7", "scc", "memory");
+    plo = __builtin_amdgcn_readfirstlane(plo);
+    phi = __builtin_amdgcn_readfirstlane(phi);
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+}
+
+// A rank-4 chunk's rotations in a 32-bit frame: a threaded loop (the lean one
+// where there is no base tile), stopping for the diagonal records, which take
+// the compiled path here.
+template <typename T, bool LEAN>
+__device__ __forceinline__ void apply_chunk(Cx<T> (&amp)[16], uint32_t k0, uint64_t tbase,
+                                            const RotRec<T> *__restrict__ rots, uint32_t count) {
+    const uint64_t p0 = (uint64_t)rots;
+    uint32_t plo = __builtin_amdgcn_readfirstlane((uint32_t)p0);
+    uint32_t phi = __builtin_amdgcn_readfirstlane((uint32_t)(p0 >> 32));
+    uint32_t cnt = __builtin_amdgcn_readfirstlane(count);
+    while (true) {
+        if constexpr (LEAN)
+            rot_lean(amp, k0, plo, phi, cnt);
+        else
+            rot_loop(amp, k0, tbase, plo, phi, cnt);
+        if (cnt == 0u) break;
+        // the record's fields through the constant address space (scalar
+        // loads: the pointer is uniform)
+        typedef const __attribute__((address_space(4))) RotRec<T> *ConstRec;
+        const ConstRec rp = (ConstRec)((((uint64_t)phi) << 32) | plo);
+        const uint64_t rz = rp->z, rzhigh = rp->zhigh;
+        const uint32_t info = rp->info;
+        const T tau_a = rp->tau_a;
+        const uint32_t zeta = (info >> 8) & 0xffu;
+        const uint32_t tpar =
+            __builtin_amdgcn_readfirstlane((uint32_t)__builtin_popcountll(tbase & rzhigh));
+        uint32_t c;
+        asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(c) : "v"(k0 & (uint32_t)rz), "s"(tpar));
+        if constexpr (sizeof(T) == 4) {
+            uint32_t ua;
+            asm("v_lshl_add_u32 %0, %1, 31, %2"
+                : "=v"(ua)
+                : "v"(c), "s"(__builtin_amdgcn_readfirstlane(__float_as_uint(tau_a))));
+            rot_diag<T, 4>(amp, __uint_as_float(ua), zeta);
+        } else {
+            rot_diag<T, 4>(amp, pin(flip_add(tau_a, c)), zeta);
+        }
+        const uint64_t pn = (((uint64_t)phi << 32) | plo) + sizeof(RotRec<T>);
+        plo = (uint32_t)pn;
+        phi = (uint32_t)(pn >> 32);
+        cnt -= 1u;
+    }
+}
+
 // Applies rotations [0, count) of `rots` to the thread's coset.
 // k0: coset representative in the frame of rec.z (32-bit in a tile frame);
 // tbase: the tile index whose parity with rec.zhigh adds to the sign (0 for
@@ -371,41 +459,7 @@ template <typename T, int M, typename K0>
 __device__ __forceinline__ void apply_rots(Cx<T> (&amp)[1 << M], K0 k0, uint64_t tbase,
                                            const RotRec<T> *__restrict__ rots, uint32_t count) {
     if constexpr (M == 4 && sizeof(K0) == 4) {
-        // rank-4 tile chunks: the threaded loop, stopping for the diagonal
-        // records, which take the compiled path below
-        const uint64_t p0 = (uint64_t)rots;
-        uint32_t plo = __builtin_amdgcn_readfirstlane((uint32_t)p0);
-        uint32_t phi = __builtin_amdgcn_readfirstlane((uint32_t)(p0 >> 32));
-        uint32_t cnt = __builtin_amdgcn_readfirstlane(count);
-        while (true) {
-            rot_loop(amp, k0, tbase, plo, phi, cnt);
-            if (cnt == 0u) break;
-            // the record's fields through the constant address space (scalar
-            // loads: the pointer is uniform)
-            typedef const __attribute__((address_space(4))) RotRec<T> *ConstRec;
-            const ConstRec rp = (ConstRec)((((uint64_t)phi) << 32) | plo);
-            const uint64_t rz = rp->z, rzhigh = rp->zhigh;
-            const uint32_t info = rp->info;
-            const T tau_a = rp->tau_a;
-            const uint32_t zeta = (info >> 8) & 0xffu;
-            const uint32_t tpar =
-                __builtin_amdgcn_readfirstlane((uint32_t)__builtin_popcountll(tbase & rzhigh));
-            uint32_t c;
-            asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(c) : "v"(k0 & (uint32_t)rz), "s"(tpar));
-            if constexpr (sizeof(T) == 4) {
-                uint32_t ua;
-                asm("v_lshl_add_u32 %0, %1, 31, %2"
-                    : "=v"(ua)
-                    : "v"(c), "s"(__builtin_amdgcn_readfirstlane(__float_as_uint(tau_a))));
-                rot_diag<T, M>(amp, __uint_as_float(ua), zeta);
-            } else {
-                rot_diag<T, M>(amp, pin(flip_add(tau_a, c)), zeta);
-            }
-            const uint64_t pn = (((uint64_t)phi << 32) | plo) + sizeof(RotRec<T>);
-            plo = (uint32_t)pn;
-            phi = (uint32_t)(pn >> 32);
-            cnt -= 1u;
-        }
+        apply_chunk<T, false>(amp, k0, tbase, rots, count);
         return;
     }
     for (uint32_t r = 0; r < count; ++r) {
@@ -515,10 +569,11 @@ __device__ __forceinline__ void tile_chunks(unsigned char *lds_raw, const uint32
         apply_rots<T, M>(amp, k0, tb, rots + ch.rot_begin, ch.rot_count);
 #pragma unroll
         for (int v = 0; v < (1 << M); ++v) {
-            const T f = rec.fac[v];
-            Cx<T> o;
-            o.re = amp[v].re * f;
-            o.im = amp[v].im * f;
+            Cx<T> o = amp[v];
+            if (v) {  // (label 0 has no pending factor)
+                o.re *= rec.fac[v];
+                o.im *= rec.fac[v];
+            }
             *reinterpret_cast<Cx<T> *>(lds_raw + (k0b ^ Xb[v])) = o;
         }
         __syncthreads();

@@ -757,28 +757,32 @@ static Pass perm_pass(int n, const Layout &A, const Layout &B) {
 }
 
 // Whether a resident plan is expected to take longer than the tile passes it
-// replaces.  Times per piece (us), resident against tile passes, fitted to
-// 500-rotation Trotter, qDRIFT and random sequences:
-//   complex64, 14 qubits: rotation 0.22 / 0.14, chunk 1.0 / 0.6, launch 4.6
-//   complex128, 13:       rotation 0.19 / 0.15, chunk 1.6 / 0.6, launch 5.0
-//   complex128, 12:       rotation 0.14 / 0.14, chunk 1.3 / 0.6, launch 5.0
+// replaces.  What it takes more (us) per rotation and chunk, and what a tile
+// pass's launch costs, fitted to sorted Trotter, qDRIFT and random sequences
+// of 100 and 500 rotations:
+//   complex64, 14 qubits: rotation 0.045, chunk 0.53, launch 5.6
+//   complex128, 13:       rotation 0,     chunk 1.05, launch 4.5
+//   complex128, 12:       rotation -0.02, chunk 0.56, launch 4.3
 // so one CU loses only where many rotations share few frames: a sorted Trotter
-// step at 13 qubits in complex128 takes 210 us resident and 151 us in 9 tile
-// passes; a qDRIFT sequence 251 us against 292 us in 31.  Below these sizes a
-// pass's launch alone outweighs the difference.
+// step of 500 terms at 13 qubits in complex128 takes 185 us resident and 148
+// us in 9 tile passes, a qDRIFT sequence 220 us against 313 us in 44.  Below
+// these sizes the launches outweigh the difference (complex64, 13 qubits: 118
+// us against 136 for the Trotter step).
 static bool resident_loses(const prx_plan &P) {
     double rot, chunk, pass;
     if (P.dtype == PRX_C64 && P.n == 14)
-        rot = 0.08, chunk = 0.4, pass = 4.6;
-    else if (P.dtype == PRX_C128 && P.n >= 12)
-        rot = P.n == 13 ? 0.04 : 0.0, chunk = P.n == 13 ? 1.0 : 0.7, pass = 5.0;
+        rot = 0.045, chunk = 0.53, pass = 5.6;
+    else if (P.dtype == PRX_C128 && P.n == 13)
+        rot = 0.0, chunk = 1.05, pass = 4.5;
+    else if (P.dtype == PRX_C128 && P.n == 12)
+        rot = -0.02, chunk = 0.56, pass = 4.3;
     else
         return false;
     const double more = rot * (double)P.rots.size() + chunk * (double)P.chunks.size();
     const int B = P.dtype == PRX_C64 ? 12 : 11, g = P.dtype == PRX_C64 ? 8 : 7;
     // it loses when the passes, less the one launch that it takes itself, cost
     // less than what it spends more in them
-    const size_t most = (size_t)(more / pass) + 1;
+    const size_t most = (size_t)(std::max(0.0, more) / pass) + 1;
     return model_passes(P.rots, 0, P.rots.size(), Layout{}, B - g, g, 128, nullptr, most + 1) <= most;
 }
 
@@ -847,6 +851,7 @@ static void pack_records(prx_plan &P, const std::vector<RotRecD> &recs) {
         r.z = recs[i].z;
         r.zhigh = recs[i].zhigh;
         r.info = recs[i].info;
+        r.jump = ((r.info >> 16) & 0xffu) * kLeanStride<T>;
         r.tau_a = (T)(recs[i].fold ? -recs[i].tau_a : recs[i].tau_a);
         r.tau_b = (T)recs[i].tau_b;
         out[i] = r;

@@ -148,17 +148,18 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
 #pragma unroll
             for (int v = 0; v < PER; ++v)
                 amp[v] = *reinterpret_cast<const Cx<T> *>(lds_raw + (k0b ^ Xb[v]));
-            apply_rots<T, M>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
+            apply_chunk<T, true>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
             double sc = ch.scale;
             if (kRenorm<T> && (ch.flags & kChunkRenormIn)) sc *= rn;
             const T s = (T)sc;
             double nrm = 0.0;
 #pragma unroll
             for (int v = 0; v < PER; ++v) {
-                const T f = rec.fac[v];
-                Cx<T> o;
-                o.re = amp[v].re * f;
-                o.im = amp[v].im * f;
+                Cx<T> o = amp[v];
+                if (v) {  // (label 0 has no pending factor)
+                    o.re *= rec.fac[v];
+                    o.im *= rec.fac[v];
+                }
                 if (ch.flags & kChunkPassEnd) {
                     o.re *= s;
                     o.im *= s;
