@@ -60,7 +60,8 @@ def kernel_sources_digest() -> str:
     h = hashlib.sha256()
     for f in ("kernels.hip", "device.h", "resident.h", "internal.h", "rot_jump_f32m4.inc",
               "rot_loop_f32m4.inc", "rot_jump_f64m4.inc", "rot_loop_f64m4.inc",
-              "rot_lean_f32m4.inc", "rot_lean_f64m4.inc"):
+              "rot_lean_f32m4.inc", "rot_lean_f64m4.inc",
+              "rot_lean_tile_f32m4.inc", "rot_lean_tile_f64m4.inc"):
         with open(os.path.join(ROOT, "paper_2504_17881_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

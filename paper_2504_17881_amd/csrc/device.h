@@ -407,10 +407,53 @@ __device__ __forceinline__ void rot_lean(Cx<double> (&amp)[16], uint32_t k0, uin
     cnt = __builtin_amdgcn_readfirstlane(cnt);
 }
 
-// A rank-4 chunk's rotations in a 32-bit frame: a threaded loop (the lean one
-// where there is no base tile), stopping for the diagonal records, which take
-// the compiled path here.
-template <typename T, bool LEAN>
+// The same for tile chunks.
+#include "rot_lean_tile_f32m4.inc"
+__device__ __forceinline__ void rot_lean_tile(Cx<float> (&amp)[16], uint32_t k0, uint64_t tb,
+                                              uint32_t &plo, uint32_t &phi, uint32_t &cnt) {
+    uint32_t ga, gb;
+    asm volatile(PRX_ROT_LEAN_TILE_F32M4
+        : "+v"(amp[0].re), "+v"(amp[0].im), "+v"(amp[1].re), "+v"(amp[1].im),
+          "+v"(amp[2].re), "+v"(amp[2].im), "+v"(amp[3].re), "+v"(amp[3].im),
+          "+v"(amp[4].re), "+v"(amp[4].im), "+v"(amp[5].re), "+v"(amp[5].im),
+          "+v"(amp[6].re), "+v"(amp[6].im), "+v"(amp[7].re), "+v"(amp[7].im),
+          "+v"(amp[8].re), "+v"(amp[8].im), "+v"(amp[9].re), "+v"(amp[9].im),
+          "+v"(amp[10].re), "+v"(amp[10].im), "+v"(amp[11].re), "+v"(amp[11].im),
+          "+v"(amp[12].re), "+v"(amp[12].im), "+v"(amp[13].re), "+v"(amp[13].im),
+          "+v"(amp[14].re), "+v"(amp[14].im), "+v"(amp[15].re), "+v"(amp[15].im),
+          "+{s76}"(plo), "+{s77}"(phi), "+{s78}"(cnt), [ga] "=&v"(ga), [gb] "=&v"(gb)
+        : [k0] "v"(k0), [tb] "s"(tb)
+        : "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87",
+          "s92", "s93", "s94", "s95", "scc", "memory");
+    plo = __builtin_amdgcn_readfirstlane(plo);
+    phi = __builtin_amdgcn_readfirstlane(phi);
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+}
+#include "rot_lean_tile_f64m4.inc"
+__device__ __forceinline__ void rot_lean_tile(Cx<double> (&amp)[16], uint32_t k0, uint64_t tb,
+                                              uint32_t &plo, uint32_t &phi, uint32_t &cnt) {
+    asm volatile(PRX_ROT_LEAN_TILE_F64M4
+        : "+v"(amp[0].re), "+v"(amp[0].im), "+v"(amp[1].re), "+v"(amp[1].im),
+          "+v"(amp[2].re), "+v"(amp[2].im), "+v"(amp[3].re), "+v"(amp[3].im),
+          "+v"(amp[4].re), "+v"(amp[4].im), "+v"(amp[5].re), "+v"(amp[5].im),
+          "+v"(amp[6].re), "+v"(amp[6].im), "+v"(amp[7].re), "+v"(amp[7].im),
+          "+v"(amp[8].re), "+v"(amp[8].im), "+v"(amp[9].re), "+v"(amp[9].im),
+          "+v"(amp[10].re), "+v"(amp[10].im), "+v"(amp[11].re), "+v"(amp[11].im),
+          "+v"(amp[12].re), "+v"(amp[12].im), "+v"(amp[13].re), "+v"(amp[13].im),
+          "+v"(amp[14].re), "+v"(amp[14].im), "+v"(amp[15].re), "+v"(amp[15].im),
+          "+{s76}"(plo), "+{s77}"(phi), "+{s78}"(cnt)
+        : [k0] "v"(k0), [tb] "s"(tb)
+        : "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87",
+          "s88", "s89", "s92", "s93", "s94", "s95", "v4", "v5", "v6", "v7", "scc", "memory");
+    plo = __builtin_amdgcn_readfirstlane(plo);
+    phi = __builtin_amdgcn_readfirstlane(phi);
+    cnt = __builtin_amdgcn_readfirstlane(cnt);
+}
+
+// A rank-4 chunk's rotations in a 32-bit frame: a threaded loop, stopping for
+// the diagonal records, which take the compiled path here.
+enum RotLoop { kRotLoop, kRotLean, kRotLeanTile };
+template <typename T, RotLoop LOOP>
 __device__ __forceinline__ void apply_chunk(Cx<T> (&amp)[16], uint32_t k0, uint64_t tbase,
                                             const RotRec<T> *__restrict__ rots, uint32_t count) {
     const uint64_t p0 = (uint64_t)rots;
@@ -418,8 +461,10 @@ __device__ __forceinline__ void apply_chunk(Cx<T> (&amp)[16], uint32_t k0, uint6
     uint32_t phi = __builtin_amdgcn_readfirstlane((uint32_t)(p0 >> 32));
     uint32_t cnt = __builtin_amdgcn_readfirstlane(count);
     while (true) {
-        if constexpr (LEAN)
+        if constexpr (LOOP == kRotLean)
             rot_lean(amp, k0, plo, phi, cnt);
+        else if constexpr (LOOP == kRotLeanTile)
+            rot_lean_tile(amp, k0, tbase, plo, phi, cnt);
         else
             rot_loop(amp, k0, tbase, plo, phi, cnt);
         if (cnt == 0u) break;
@@ -458,10 +503,6 @@ __device__ __forceinline__ void apply_chunk(Cx<T> (&amp)[16], uint32_t k0, uint6
 template <typename T, int M, typename K0>
 __device__ __forceinline__ void apply_rots(Cx<T> (&amp)[1 << M], K0 k0, uint64_t tbase,
                                            const RotRec<T> *__restrict__ rots, uint32_t count) {
-    if constexpr (M == 4 && sizeof(K0) == 4) {
-        apply_chunk<T, false>(amp, k0, tbase, rots, count);
-        return;
-    }
     for (uint32_t r = 0; r < count; ++r) {
         const RotRec<T> rec = rots[r];
         const uint32_t slot = rec.info & 15u;
@@ -542,7 +583,7 @@ __device__ __forceinline__ void tile_thread_masks(uint32_t tid, uint32_t (&tmask
     for (int i = 0; i < NB; ++i) tmask[i] = pin(0u - ((tid >> i) & 1u));
 }
 
-template <typename T, int B, int M>
+template <typename T, int B, int M, RotLoop LOOP>
 __device__ __forceinline__ void tile_chunks(unsigned char *lds_raw, const uint32_t (&tmask)[B - M],
                                             uint64_t tb, const ChunkRec<T> *__restrict__ chunks,
                                             uint32_t count, const RotRec<T> *__restrict__ rots) {
@@ -566,7 +607,10 @@ __device__ __forceinline__ void tile_chunks(unsigned char *lds_raw, const uint32
 #pragma unroll
         for (int v = 0; v < (1 << M); ++v)
             amp[v] = *reinterpret_cast<const Cx<T> *>(lds_raw + (k0b ^ Xb[v]));
-        apply_rots<T, M>(amp, k0, tb, rots + ch.rot_begin, ch.rot_count);
+        if constexpr (M == 4)
+            apply_chunk<T, LOOP>(amp, k0, tb, rots + ch.rot_begin, ch.rot_count);
+        else
+            apply_rots<T, M>(amp, k0, tb, rots + ch.rot_begin, ch.rot_count);
 #pragma unroll
         for (int v = 0; v < (1 << M); ++v) {
             Cx<T> o = amp[v];

@@ -40,16 +40,18 @@ named on its own; variants are 404 bytes and the table must be followed by
 40 readable bytes.  Extra operands: %[sg] (a register pair) and %[t]
 scratch; it also clobbers s[92:93].
 
-rot_lean_f32m4.inc and rot_lean_f64m4.inc are the loops of resident states,
-where one wave per SIMD leaves nothing to hide the dispatch behind, so its
-instructions count.  The record's pad word holds the variant's byte offset in
+rot_lean_f32m4.inc and rot_lean_f64m4.inc are the loops of resident states, and
+rot_lean_tile_*.inc those of tile chunks.  One wave per SIMD leaves nothing to
+hide the dispatch behind, so its instructions count.  The record's pad word holds the variant's byte offset in
 the table (the host's var * stride; 64 * stride for a diagonal record, which
 is the exit that puts it back), the table's address is taken once, the count
-ends the loop by its borrow, and there is no base tile: 12 scalar instructions
-less per rotation than rot_loop.  complex128 sets the sign in the high words
+ends the loop by its borrow: 10 scalar instructions less per rotation than
+rot_loop, 12 where there is no base tile.  complex128 sets the sign in the high words
 of fixed registers v[4:7].  Operands: %0..%31 the amplitudes, %[k0]; complex64 also
 %[ga], %[gb]; the record pointer is in s[76:77] and the count in s78, read and
-written.  They clobber s[80:89], s[92:95] and SCC (complex128 also v[4:7]); variants are 324 and 340 bytes.
+written.  They clobber s[80:89], s[92:95] and SCC (complex128 also v[4:7]);
+variants are 324 and 340 bytes.  Those of tile chunks also take %[tb], clobber
+s79 and are 8 bytes longer.
 
 Run from this directory: python3 gen_rot_jump.py
 """
@@ -212,14 +214,14 @@ LEAN_VARIANT_BYTES = 32 * 8 + 68
 LEAN64_VARIANT_BYTES = 32 * 8 + 84
 
 
-def lean_block(f64=False):
+def lean_block(f64=False, tile=False):
     size = 40 if f64 else 32
     loads = ["s_load_dwordx8 s[80:87], s[76:77], 0x0"]
     if f64:
         loads.append("s_load_dwordx2 s[88:89], s[76:77], 0x20")
         ga, gb, op = "v[4:5]", "v[6:7]", "v_fma_f64"
         coef = ["v_and_b32 v5, s80, %[k0]",
-                "v_bcnt_u32_b32 v7, v5, 0",
+                f"v_bcnt_u32_b32 v7, v5, {'s79' if tile else 0}",
                 "v_mov_b32 v4, s86",
                 "v_lshl_add_u32 v5, v7, 31, s87",
                 "v_mov_b32 v6, s88",
@@ -227,9 +229,11 @@ def lean_block(f64=False):
     else:
         ga, gb, op = "%[ga]", "%[gb]", "v_fma_f32"
         coef = ["v_and_b32 %[ga], s80, %[k0]",
-                "v_bcnt_u32_b32 %[ga], %[ga], 0",
+                f"v_bcnt_u32_b32 %[ga], %[ga], {'s79' if tile else 0}",
                 "v_lshl_add_u32 %[gb], %[ga], 31, s87",
                 "v_lshl_add_u32 %[ga], %[ga], 31, s86"]
+    if tile:
+        coef = ["s_and_b64 s[82:83], s[82:83], %[tb]", "s_bcnt1_i32_b64 s79, s[82:83]"] + coef
     dispatch = (["s_sub_u32 s78, s78, 1",          # borrow: no record left
                  "s_cbranch_scc1 8f",
                  "s_waitcnt lgkmcnt(0)",
@@ -295,15 +299,17 @@ def main():
                 f'    "{line}\\n"' for line in loop_block64()) + "\n")
     with open(os.path.join(here, "rot_loop_f64m4.inc"), "w") as f:
         f.write(text)
-    for name, f64, size in (("F32", False, LEAN_VARIANT_BYTES), ("F64", True, LEAN64_VARIANT_BYTES)):
-        text = ("// Generated by gen_rot_jump.py; do not edit.\n"
-                f"// Rotation loop of resident states, {'complex128' if f64 else 'complex64'}, rank 4\n"
-                "// (operands and layout: see gen_rot_jump.py).\n"
-                "#pragma once\n"
-                f"#define PRX_ROT_LEAN_{name}M4 \\\n" + " \\\n".join(
-                    f'    "{line}\\n"' for line in lean_block(f64)) + "\n")
-        with open(os.path.join(here, f"rot_lean_{name.lower()}m4.inc"), "w") as f:
-            f.write(text)
+    for name, f64 in (("F32", False), ("F64", True)):
+        for kind, tile in (("LEAN", False), ("LEAN_TILE", True)):
+            text = ("// Generated by gen_rot_jump.py; do not edit.\n"
+                    f"// Lean rotation loop of {'tile chunks' if tile else 'resident states'}, "
+                    f"{'complex128' if f64 else 'complex64'}, rank 4\n"
+                    "// (operands and layout: see gen_rot_jump.py).\n"
+                    "#pragma once\n"
+                    f"#define PRX_ROT_{kind}_{name}M4 \\\n" + " \\\n".join(
+                        f'    "{line}\\n"' for line in lean_block(f64, tile)) + "\n")
+            with open(os.path.join(here, f"rot_{kind.lower()}_{name.lower()}m4.inc"), "w") as f:
+                f.write(text)
 
 
 if __name__ == "__main__":

@@ -52,7 +52,8 @@ prx_status hip_fail(hipError_t e, const char *what);
 //            bit  5    static-sign variant (chunk rank <= kStaticSignRank)
 //            bits 8-15 zeta: bit i = parity(basis_i & z)
 //            bits 16-23 variant index (static-sign chunks)
-//   jump   : variant index times kLeanStride<T> (see gen_rot_jump.py)
+//   jump   : variant index times the stride of the lean loop of the plan's
+//            kind (resident or tile chunks)
 //   tau_a, tau_b : signed magnitudes (real or imaginary parts); for x = 0
 //            only tau_a is used (tan(phi))
 template <typename T>
@@ -60,14 +61,16 @@ struct RotRec {
     uint64_t z;
     uint64_t zhigh;
     uint32_t info;
-    uint32_t jump;  // rank-4 records: the variant's byte offset in the lean loop's table
+    uint32_t jump;  // rank-4 records: the variant's byte offset in the lean loops' tables
     T tau_a;
     T tau_b;
 };
 
-// Bytes of one variant of the lean rotation loop (checked against its assembly).
+// Bytes of one variant of the lean rotation loop of resident states, and what
+// those of tile chunks have more (checked against the built code).
 template <typename T>
 static constexpr uint32_t kLeanStride = sizeof(T) == 4 ? 324u : 340u;
+static constexpr uint32_t kLeanTileMore = 8u;
 
 static constexpr uint32_t kSlotDiag = 15;
 // Chunks of rank up to kStaticSignRank run one compiled variant per

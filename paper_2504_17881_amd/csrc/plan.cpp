@@ -851,7 +851,7 @@ static void pack_records(prx_plan &P, const std::vector<RotRecD> &recs) {
         r.z = recs[i].z;
         r.zhigh = recs[i].zhigh;
         r.info = recs[i].info;
-        r.jump = ((r.info >> 16) & 0xffu) * kLeanStride<T>;
+        r.jump = ((r.info >> 16) & 0xffu) * (kLeanStride<T> + (P.resident ? 0u : kLeanTileMore));
         r.tau_a = (T)(recs[i].fold ? -recs[i].tau_a : recs[i].tau_a);
         r.tau_b = (T)recs[i].tau_b;
         out[i] = r;

@@ -148,7 +148,7 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
 #pragma unroll
             for (int v = 0; v < PER; ++v)
                 amp[v] = *reinterpret_cast<const Cx<T> *>(lds_raw + (k0b ^ Xb[v]));
-            apply_chunk<T, true>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
+            apply_chunk<T, kRotLean>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
             double sc = ch.scale;
             if (kRenorm<T> && (ch.flags & kChunkRenormIn)) sc *= rn;
             const T s = (T)sc;

@@ -21,10 +21,11 @@ def _gen():
 
 def test_loops_are_generated_and_wait_for_their_loads():
     gen = _gen()
-    for f64, name in ((False, "F32"), (True, "F64")):
-        with open(os.path.join(CSRC, f"rot_lean_{name.lower()}m4.inc")) as f:
+    for f64, tile in ((False, False), (True, False), (False, True), (True, True)):
+        name = f"rot_lean{'_tile' if tile else ''}_{'f64' if f64 else 'f32'}m4.inc"
+        with open(os.path.join(CSRC, name)) as f:
             text = f.read()
-        lines = gen.lean_block(f64)
+        lines = gen.lean_block(f64, tile)
         assert [ln.split('"')[1][:-2] for ln in text.splitlines() if ln.startswith('    "')] == lines
         # the only ways out pass a wait for the record loaded ahead
         assert lines[lines.index("8:") + 1] == "s_waitcnt lgkmcnt(0)"
@@ -41,17 +42,18 @@ def test_layout_in_built_code(tmp_path, obj_name):
     addr = [a for a, _, _ in ins]
     at = {a: i for i, a in enumerate(addr)}
     jumps = [i for i, (_, op, txt) in enumerate(ins) if op == "s_setpc_b64" and "s[94:95]" in txt]
-    heads = [i for i in jumps if any(op == "s_getpc_b64" for _, op, _ in ins[i - 18:i])]
+    heads = [i for i in jumps if any(op == "s_getpc_b64" for _, op, _ in ins[i - 20:i])]
     assert len(jumps) == 65 * len(heads)
     seen = set()
     for i in heads:
-        g = max(j for j in range(i - 18, i) if ins[j][1] == "s_getpc_b64")
+        g = max(j for j in range(i - 20, i) if ins[j][1] == "s_getpc_b64")
         assert "s[92:93]" in ins[g][2]
         off = int(ins[g + 1][2].rsplit(",", 1)[1].strip(), 0)
         start = addr[i + 1]
         assert addr[g + 1] + off == start         # the table follows the head's jump
         f64 = ins[i + 2][1] == "s_load_dwordx2"
-        stride = gen.LEAN64_VARIANT_BYTES if f64 else gen.LEAN_VARIANT_BYTES
+        tile = any(op == "s_bcnt1_i32_b64" for _, op, _ in ins[g:i])
+        stride = (gen.LEAN64_VARIANT_BYTES if f64 else gen.LEAN_VARIANT_BYTES) + 8 * tile
         lead = 2 if f64 else 1
         seen.add(stride)
         end = None
@@ -72,8 +74,9 @@ def test_layout_in_built_code(tmp_path, obj_name):
         assert [op for _, op, _ in ins[j + 1:j + 4]] == ["s_subb_u32", "s_add_u32", "s_branch"]
         assert ins[at[end]][1] == "s_waitcnt"
         assert _branch_target(ins, j + 3) == addr[at[end] + 2]
-    assert seen == {324, 340}
+    assert seen == {324, 340, 332, 348}
     # the records' offsets use the same strides
     with open(os.path.join(CSRC, "internal.h")) as f:
-        assert "sizeof(T) == 4 ? 324u : 340u" in f.read()
+        text = f.read()
+    assert "sizeof(T) == 4 ? 324u : 340u" in text and "kLeanTileMore = 8u" in text
     assert (gen.LEAN_VARIANT_BYTES, gen.LEAN64_VARIANT_BYTES) == (324, 340)
