@@ -416,7 +416,8 @@ prx_status prx_batch_run(size_t S, void *const *psi, const int *n,
 
 /* HIP graphs of a batch execution or of a plan's pass sequence, captured on
  * `stream` (which must not be the default stream) and instantiated; replay
- * with prx_graph_launch on any stream. */
+ * with prx_graph_launch on any stream.  A batch's graph runs the samples that
+ * stay in LDS beside the rounds of the others. */
 prx_status prx_batch_graph(const prx_batch *b, void *ws, size_t ws_bytes,
                            double *overlaps_dev, void *stream, prx_graph **out);
 prx_status prx_plan_graph(const prx_plan *plan, void *psi, void *ws, size_t ws_bytes,
