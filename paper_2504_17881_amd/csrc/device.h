@@ -624,11 +624,37 @@ __device__ __forceinline__ void tile_chunks(unsigned char *lds_raw, const uint32
     }
 }
 
+// v of the lane that the DPP control names (all lanes active).
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// FP64 sum over a wave, in every lane (all lanes active), as a butterfly of
+// growing distance (a 64-bit LDS permute per step costs its latency twice, 6
+// steps about 0.3 us at the end of every pass and again in the next one).
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_move<0xb1>(v);   // quad_perm 1 0 3 2
+    v += dpp_move<0x4e>(v);   // quad_perm 2 3 0 1
+    v += dpp_move<0x141>(v);  // row_half_mirror: the other quad of eight lanes
+    v += dpp_move<0x140>(v);  // row_mirror: the other eight of a row
+    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
+}
+
 // FP64 block sum of one value per thread; result valid in thread 0.
 template <int NT>
 __device__ __forceinline__ double block_sum(double v, double *red) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    v = wave_sum(v);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if constexpr (NT > 64) {
         if (lane == 0) red[wave] = v;

@@ -167,9 +167,12 @@ struct RenormIn {
     const double *p;
     unsigned count;
 };
-// Partials a pass sums itself (every wave reads them all, 2 KB at most: 4 per
-// lane at 256, where the wait hides behind the state's loads).
-static constexpr unsigned kRenormDirect = 256;
+// Partials a pass sums itself (every wave reads them all, 4 KB at most: 8 per
+// lane at 512).  A 200-rotation qDRIFT plan of 22 qubits, whose passes leave
+// 512: 271 us through a launch of its own, 253 summed by the next pass.  With
+// 1024 the gain is used up (12-qubit frames at 22 qubits: 605 / 607 us), with
+// 2048 the sums cost more than the launch (23 qubits: 1081 / 1231).
+static constexpr unsigned kRenormDirect = 512;
 static constexpr unsigned kRenormOneBlock = 16384;
 
 // Arguments of a single-rotation sweep.

@@ -172,8 +172,7 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
             }
             if (kRenorm<T> && (ch.flags & kChunkNormOut)) {
                 if (tid >= ncos) nrm = 0.0;
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
+                nrm = wave_sum(nrm);
                 if ((tid & 63u) == 0) red[par][wave] = nrm;
             }
         }

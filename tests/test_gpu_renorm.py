@@ -1,5 +1,5 @@
 """The complex64 renormalisation hand-off between passes: summed by the next
-pass (up to 256 partials), by one workgroup, or by two launches, and the
+pass (up to 512 partials), by one workgroup, or by two launches, and the
 changes from one form to another within a plan.
 
 The input has norm 3, so only a plan whose hand-offs all carry the right norm
@@ -20,8 +20,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,M,opts", [
     (16, 200, dict(tile_qubits=12, max_virtual=4)),              # 16 partials
-    (20, 120, dict(tile_qubits=12)),                             # 256: the longest direct sum
-    (21, 120, dict(tile_qubits=12)),                             # 512: one workgroup
+    (20, 120, dict(tile_qubits=12)),                             # 256: four loads per lane
+    (21, 120, dict(tile_qubits=12)),                             # 512: the longest direct sum
+    (18, 120, dict(tile_qubits=12)),                             # 64: one load per lane
+    (22, 60, dict(tile_qubits=12)),                              # 1024: one workgroup
     (17, 200, dict(tile_qubits=10, max_grid=100)),               # capped grid, ragged count
     (20, 120, dict(tile_qubits=14, max_virtual=10)),             # persistent workgroups
     (18, 300, dict(tile_qubits=13, max_virtual=3, span_max=4)),  # spans and tiles mixed
