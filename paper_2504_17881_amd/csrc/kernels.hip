@@ -29,6 +29,7 @@
 // psi'), tau = beta / cos(phi); a pass multiplies its cosines (and an FP64
 // renormalisation factor) into one scale applied at the store.
 
+#include <cmath>
 #include <mutex>
 
 #include "resident.h"
@@ -162,7 +163,14 @@ __device__ __forceinline__ double renorm_factor(const RenormIn &in) {
 
 // ------------------------------------------------------------------ span
 
-template <typename T, int M>
+// The accesses are non-temporal where the tile passes' are (streams_state): an
+// ordinary pass in between leaves its results dirty in the L2s, which are
+// written back at its end, and the next pass starts cold.  Measured, ordinary /
+// non-temporal (us): one span among the 12 tile passes of a 200-rotation qDRIFT
+// plan of 22 qubits complex64 255 / 230, among the 9 of a 20-qubit Trotter step
+// 134 / 127; three spans of 27 qubits 1254 / 1182, of 20 qubits complex128 24.8
+// / 21.6.  (Three spans alone at 22 qubits complex64, the L2s' size, 39 / 43.)
+template <typename T, int M, bool STREAM>
 __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs a,
                                               const RotRec<T> *__restrict__ rots,
                                               RenormIn renorm_in,
@@ -190,7 +198,7 @@ __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs 
         Cx<T> amp[1 << M];
         if (live) {
 #pragma unroll
-            for (int v = 0; v < (1 << M); ++v) amp[v] = psi[k0 ^ X[v]];
+            for (int v = 0; v < (1 << M); ++v) amp[v] = amp_load<STREAM>(psi + (k0 ^ X[v]));
         }
         apply_rots<T, M>(amp, k0, 0, rots + a.rot_begin, a.rot_count);
         if (live) {
@@ -201,7 +209,7 @@ __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs 
                 Cx<T> o;
                 o.re = amp[v].re * s;
                 o.im = amp[v].im * s;
-                psi[k0 ^ X[v]] = o;
+                amp_store<STREAM>(psi + (k0 ^ X[v]), o);
                 if constexpr (kRenorm<T>) {
                     nrm = fma((double)o.re, (double)o.re, nrm);
                     nrm = fma((double)o.im, (double)o.im, nrm);
@@ -685,17 +693,26 @@ static unsigned tile_grid(const void *kernel, int n, int B, int threads, unsigne
 
 bool span_supported(prx_dtype, int m) { return m >= 1 && m <= 5; }
 
+template <typename T, int M>
+static void span_one(Cx<T> *p, const SpanArgs &a, const RotRec<T> *r, const RenormIn &rin,
+                     double *nout, hipStream_t s, unsigned nb) {
+    if (streams_state(std::ldexp((double)sizeof(Cx<T>), a.n)))
+        hipLaunchKernelGGL((k_span<T, M, true>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout);
+    else
+        hipLaunchKernelGGL((k_span<T, M, false>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout);
+}
+
 template <typename T>
 static hipError_t span_t(int m, void *psi, const SpanArgs &a, const void *rots,
                          const RenormIn &rin, double *nout, hipStream_t s, unsigned nb) {
     const RotRec<T> *r = (const RotRec<T> *)rots;
     Cx<T> *p = (Cx<T> *)psi;
     switch (m) {
-    case 1: hipLaunchKernelGGL((k_span<T, 1>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout); break;
-    case 2: hipLaunchKernelGGL((k_span<T, 2>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout); break;
-    case 3: hipLaunchKernelGGL((k_span<T, 3>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout); break;
-    case 4: hipLaunchKernelGGL((k_span<T, 4>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout); break;
-    case 5: hipLaunchKernelGGL((k_span<T, 5>), dim3(nb), dim3(256), 0, s, p, a, r, rin, nout); break;
+    case 1: span_one<T, 1>(p, a, r, rin, nout, s, nb); break;
+    case 2: span_one<T, 2>(p, a, r, rin, nout, s, nb); break;
+    case 3: span_one<T, 3>(p, a, r, rin, nout, s, nb); break;
+    case 4: span_one<T, 4>(p, a, r, rin, nout, s, nb); break;
+    case 5: span_one<T, 5>(p, a, r, rin, nout, s, nb); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -38,6 +38,26 @@ __device__ __forceinline__ void group_store(Cx<T> *p, const typename Group<T>::V
         *reinterpret_cast<V *>(p) = v;
 }
 
+// One amplitude.
+template <bool NT, typename T>
+__device__ __forceinline__ Cx<T> amp_load(const Cx<T> *p) {
+    typedef T W __attribute__((ext_vector_type(2)));
+    if constexpr (NT) {
+        const W w = __builtin_nontemporal_load(reinterpret_cast<const W *>(p));
+        return Cx<T>{w.x, w.y};
+    } else {
+        return *p;
+    }
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void amp_store(Cx<T> *p, const Cx<T> &v) {
+    typedef T W __attribute__((ext_vector_type(2)));
+    if constexpr (NT)
+        __builtin_nontemporal_store(W{v.re, v.im}, reinterpret_cast<W *>(p));
+    else
+        *p = v;
+}
+
 // A 128 KiB tile-set (14 qubits at complex64, 13 at complex128) fills most
 // of the CU's 160 KiB of LDS, so one workgroup runs per CU; it runs
 // persistently, striding over the tile-sets and loading the next one into
