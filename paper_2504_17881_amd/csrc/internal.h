@@ -145,6 +145,17 @@ static inline bool streams_state(double bytes) {
     return bytes <= 32.0 * 1048576.0 || bytes > 256.0 * 1048576.0;
 }
 
+// State accesses of a plain sweep, which has nothing else to wait for.  States
+// above 256 MiB stream (us per sweep, ordinary / non-temporal: 28 qubits
+// complex64 pair 781 / 727, diagonal 764 / 686; 26 qubits complex128 378 / 346
+// and 384 / 336).  A sequence of sweeps over a smaller state is best served by
+// the L2s and the last-level cache (18 qubits complex64 3.2 / 3.4, 22 qubits
+// 10.8 / 12.0, 24 qubits alike), except that a sweep beside the streaming
+// passes of a fused plan goes with them.
+static inline bool plain_streams(double bytes, bool beside_fused) {
+    return beside_fused ? streams_state(bytes) : bytes > 256.0 * 1048576.0;
+}
+
 // Kernel arguments of a tile pass.
 struct TileArgs {
     // Slot s = tid + u NT of the tile-set holds amplitude
@@ -182,6 +193,7 @@ struct PlainArgs {
     int pivot;       // highest set bit of x (pair kernels)
     int nY_odd;      // popcount(x & z) odd
     int beta_imag;   // beta = i^{nY+1} sin(phi) is imaginary
+    int stream;      // non-temporal state accesses (see plain_streams)
     double c;        // cos(phi)
     double beta;     // signed magnitude of beta
 };

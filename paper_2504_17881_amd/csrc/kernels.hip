@@ -41,7 +41,7 @@ namespace prx {
 // Launch grids are capped at kMaxGridBlocks workgroups (2^30 work-items at
 // 256 threads, inside the 32-bit work-item range of a dispatch); the sweep
 // kernels stride over the rest of the state.
-template <typename T, int U>
+template <typename T, int U, bool STREAM>
 __global__ void __launch_bounds__(256) k_plain_pair(Cx<T> *__restrict__ psi, PlainArgs a,
                                                     uint64_t npairs) {
     const T c = (T)a.c;
@@ -57,8 +57,8 @@ __global__ void __launch_bounds__(256) k_plain_pair(Cx<T> *__restrict__ psi, Pla
             k[i] = insert_zero64(j < npairs ? j : 0, a.pivot);
             kp[i] = k[i] ^ a.x;
             if (j < npairs) {
-                u[i] = psi[k[i]];
-                w[i] = psi[kp[i]];
+                u[i] = amp_load<STREAM>(psi + k[i]);
+                w[i] = amp_load<STREAM>(psi + kp[i]);
             }
         }
 #pragma unroll
@@ -80,13 +80,13 @@ __global__ void __launch_bounds__(256) k_plain_pair(Cx<T> *__restrict__ psi, Pla
                 nw.re = c * w[i].re + bkp * u[i].re;
                 nw.im = c * w[i].im + bkp * u[i].im;
             }
-            psi[k[i]] = nu;
-            psi[kp[i]] = nw;
+            amp_store<STREAM>(psi + k[i], nu);
+            amp_store<STREAM>(psi + kp[i], nw);
         }
     }
 }
 
-template <typename T, int U>
+template <typename T, int U, bool STREAM>
 __global__ void __launch_bounds__(256) k_plain_diag(Cx<T> *__restrict__ psi, PlainArgs a,
                                                     uint64_t N) {
     const T c = (T)a.c;
@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(256) k_plain_diag(Cx<T> *__restrict__ psi, Pla
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const uint64_t k = base + (uint64_t)i * 256u;
-            if (k < N) u[i] = psi[k];
+            if (k < N) u[i] = amp_load<STREAM>(psi + k);
         }
 #pragma unroll
         for (int i = 0; i < U; ++i) {
@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(256) k_plain_diag(Cx<T> *__restrict__ psi, Pla
             Cx<T> nu;
             nu.re = c * u[i].re - bs * u[i].im;
             nu.im = c * u[i].im + bs * u[i].re;
-            psi[k] = nu;
+            amp_store<STREAM>(psi + k, nu);
         }
     }
 }
@@ -603,13 +603,26 @@ __global__ void __launch_bounds__(1024) k_renorm_finish(const double *__restrict
     if (threadIdx.x == 0) scale_out[0] = 1.0 / sqrt(s);
 }
 
-template <typename T>
+// Bound by the bandwidth of reading and writing the state, 16 bytes per lane;
+// streaming, U groups in flight.  Measured after the norm's read, ordinary /
+// streaming (us for both): 28 qubits complex128 2579 / 2387, 26 (1 GiB) 648 /
+// 626; 25 qubits (512 MiB), half of which the last-level cache still holds,
+// 293 / 331.  Four groups in flight slow the ordinary form (256 MiB: 147 / 152).
+template <typename T, bool STREAM>
 __global__ void __launch_bounds__(256) k_scale(Cx<T> *__restrict__ a, uint64_t ngroups, T s) {
+    constexpr int G = Group<T>::G, U = STREAM ? 4 : 1;
     typedef typename Group<T>::V V;
-    V *p = reinterpret_cast<V *>(a);
     const uint64_t stride = (uint64_t)gridDim.x * 256u;
-    for (uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x; k < ngroups; k += stride)
-        p[k] = p[k] * s;
+    uint64_t k = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+    for (; k + (U - 1) * stride < ngroups; k += U * stride) {
+        V v[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) v[i] = group_load<STREAM>(a + G * (k + i * stride));
+#pragma unroll
+        for (int i = 0; i < U; ++i) group_store<STREAM>(a + G * (k + i * stride), v[i] * s);
+    }
+    for (; k < ngroups; k += stride)
+        group_store<STREAM>(a + G * k, group_load<STREAM>(a + G * k) * s);
 }
 
 // ------------------------------------------------------------- launchers
@@ -620,21 +633,22 @@ static unsigned capped_blocks(uint64_t want, unsigned cap) {
     return (unsigned)std::min<uint64_t>(want ? want : 1, c);
 }
 
+template <typename T, bool STREAM>
+static hipError_t plain_one(Cx<T> *p, const PlainArgs &a, hipStream_t s, unsigned cap) {
+    constexpr int U = 4;
+    const uint64_t items = a.x == 0 ? 1ull << a.n : 1ull << (a.n - 1);
+    const dim3 grid(capped_blocks((items + 256u * U - 1) / (256u * U), cap)), nt(256);
+    if (a.x == 0)
+        hipLaunchKernelGGL((k_plain_diag<T, U, STREAM>), grid, nt, 0, s, p, a, items);
+    else
+        hipLaunchKernelGGL((k_plain_pair<T, U, STREAM>), grid, nt, 0, s, p, a, items);
+    return hipGetLastError();
+}
+
 template <typename T>
 static hipError_t plain_t(void *psi, const PlainArgs &a, hipStream_t s, unsigned cap) {
-    constexpr int U = 4;
-    if (a.x == 0) {
-        const uint64_t N = 1ull << a.n;
-        hipLaunchKernelGGL((k_plain_diag<T, U>), dim3(capped_blocks((N + 256u * U - 1) / (256u * U), cap)),
-                           dim3(256), 0, s,
-                           (Cx<T> *)psi, a, N);
-    } else {
-        const uint64_t np = 1ull << (a.n - 1);
-        hipLaunchKernelGGL((k_plain_pair<T, U>), dim3(capped_blocks((np + 256u * U - 1) / (256u * U), cap)),
-                           dim3(256), 0, s,
-                           (Cx<T> *)psi, a, np);
-    }
-    return hipGetLastError();
+    return a.stream ? plain_one<T, true>((Cx<T> *)psi, a, s, cap)
+                    : plain_one<T, false>((Cx<T> *)psi, a, s, cap);
 }
 
 hipError_t launch_plain(prx_dtype dt, void *psi, const PlainArgs &a, hipStream_t s, unsigned cap) {
@@ -882,7 +896,12 @@ template <typename T>
 static hipError_t scale_t(void *psi, int n, double scale, hipStream_t s) {
     const uint64_t ngroups = (1ull << n) / Group<T>::G;
     const unsigned g = (unsigned)std::min<uint64_t>((ngroups + 255) / 256, 256u * 64u);
-    hipLaunchKernelGGL(k_scale<T>, dim3(g), dim3(256), 0, s, (Cx<T> *)psi, ngroups, (T)scale);
+    if (std::ldexp((double)sizeof(Cx<T>), n) >= 0x1p30)
+        hipLaunchKernelGGL((k_scale<T, true>), dim3(g), dim3(256), 0, s, (Cx<T> *)psi, ngroups,
+                           (T)scale);
+    else
+        hipLaunchKernelGGL((k_scale<T, false>), dim3(g), dim3(256), 0, s, (Cx<T> *)psi, ngroups,
+                           (T)scale);
     return hipGetLastError();
 }
 

@@ -156,7 +156,7 @@ struct SlotScale {
     }
 };
 
-static PlainArgs plain_args(int n, const KRot &r) {
+static PlainArgs plain_args(int n, const KRot &r, bool stream) {
     PlainArgs a;
     a.x = r.x;
     a.z = r.z;
@@ -166,6 +166,7 @@ static PlainArgs plain_args(int n, const KRot &r) {
     a.nY_odd = nY & 1;
     const int mq = (nY + 1) & 3;
     a.beta_imag = mq & 1;
+    a.stream = stream;
     a.c = std::cos(r.phi);
     a.beta = ((mq >= 2) ? -1.0 : 1.0) * std::sin(r.phi);
     return a;
@@ -1207,7 +1208,12 @@ static prx_status execute_impl(const prx_plan *P, void *psi, void *ws, size_t ws
         hipError_t e = hipSuccess;
         if (ev) PRX_HIP(hipEventRecord(ev[3 * i], s));
         if (ps.kind == kPlain) {
-            e = launch_plain(P->dtype, psi, plain_args(P->n, P->rots[ps.r0]), s, P->cfg.grid_cap);
+            const bool beside = (i > 0 && P->passes[i - 1].kind != kPlain) ||
+                                (i + 1 < P->passes.size() && P->passes[i + 1].kind != kPlain);
+            const bool stream =
+                plain_streams(std::ldexp(P->dtype == PRX_C64 ? 8.0 : 16.0, P->n), beside);
+            e = launch_plain(P->dtype, psi, plain_args(P->n, P->rots[ps.r0], stream), s,
+                             P->cfg.grid_cap);
         } else if (ps.kind == kPerm) {
             PermArgs a;
             std::memset(&a, 0, sizeof(a));
