@@ -129,6 +129,9 @@ __device__ __forceinline__ SetBase set_base(const TileArgs *ta, uint32_t w, uint
 // works as in k_tile: small ones one per workgroup and item; the 128 KiB ones
 // (TilePersist) in workgroups that stride over the items and hold the next
 // item's set in registers while they compute the current one.
+// The small sets' accesses are non-temporal at every size: ordinary ones where
+// a round's states fit the last-level cache took 678 against 584 us (24 samples
+// of 16 to 22 qubits complex64), 6630 against 5408 (48 of 17 to 21 complex128).
 template <typename T, int B, int M>
 __global__ void __launch_bounds__(1 << (B - M))
     __attribute__((amdgpu_waves_per_eu(TileWaves<T, B, M>::value)))

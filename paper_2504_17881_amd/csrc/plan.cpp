@@ -813,6 +813,23 @@ static void default_frames(prx_dtype dt, int n, PlanCfg &c) {
     c.max_virtual = c.B - kMinTileLow;
 }
 
+// Whether 12-qubit frames do for a complex64 plan whose state takes wider ones:
+// a pass of theirs costs 0.85 to 0.9 of a wider one (0.95 at 22 and 23 qubits),
+// so they win where the wider ones save no passes.  Measured, wide / 12-qubit:
+// 100 rotations over one high X mask, one pass each, 24 qubits 192 / 163 us, 28
+// qubits 2629 / 2109; a 200-term Trotter step of 20 qubits, 10 passes and 11,
+// 128 / 120; a qDRIFT sequence of 24 qubits, 26 passes and 34, 1606 / 1787.
+static constexpr int kNarrowC64 = 12;
+static bool narrow_suffices(const prx_plan &P) {
+    if (P.dtype != PRX_C64 || P.cfg.B <= kNarrowC64 || P.rots.empty()) return false;
+    const int low = kMinTileLow, mf = P.cfg.max_fuse;
+    const size_t N = P.rots.size();
+    const size_t wide = model_passes(P.rots, 0, N, Layout{}, low, P.cfg.B - low, mf);
+    const size_t most = P.n == 22 || P.n == 23 ? wide : wide * 10 / 9;
+    return model_passes(P.rots, 0, N, Layout{}, low, kNarrowC64 - low, mf, nullptr, most + 1) <=
+           most;
+}
+
 static void apply_opts(const prx_plan_opts *o, PlanCfg &c) {
     if (!o) return;
     if (o->tile_qubits || o->chunk_rank || o->span_max || o->max_virtual || o->tile_only > 0)
@@ -952,6 +969,11 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             } else {
                 recs.swap(bld.recs);
             }
+        }
+        if (fused && !internal && !P->resident && !P->cfg.shaped && !P->cfg.relabel &&
+            narrow_suffices(*P)) {
+            P->cfg.B = kNarrowC64;
+            P->cfg.max_virtual = kNarrowC64 - kMinTileLow;
         }
         const bool relabel = P->cfg.relabel && fused &&
                              n >= std::max(P->cfg.B + 2, 14) &&

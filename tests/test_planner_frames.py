@@ -44,13 +44,27 @@ def test_wide_frames_match_oracle(n, dtype, opts):
 ])
 def test_default_frame_sizes(dtype, sizes):
     for n, B in sizes.items():
-        x, z, phi = synth.random_pauli_rotations(n, 40, seed=n)
+        x, z, phi = synth.random_pauli_rotations(n, 140, seed=n)
         s = P.prx_sched_from_rotations(n, x, z, phi)
-        pl = P.prx_plan_create(s, n, dtype, 0, 40, P.PRX_FUSED)
+        pl = P.prx_plan_create(s, n, dtype, 0, 140, P.PRX_FUSED)
         assert P.prx_plan_get_info(pl)["tile_qubits"] == B
         P.prx_plan_destroy(pl)
         # named frames keep their defaults
-        pl = P.prx_plan_create(s, n, dtype, 0, 40, P.PRX_FUSED, dict(max_virtual=3))
+        pl = P.prx_plan_create(s, n, dtype, 0, 140, P.PRX_FUSED, dict(max_virtual=3))
         assert P.prx_plan_get_info(pl)["tile_qubits"] == (12 if dtype == P.PRX_C64 else 11)
         P.prx_plan_destroy(pl)
         P.prx_sched_destroy(s)
+
+
+@pytest.mark.parametrize("n", [19, 22, 23, 28])
+def test_narrow_frames_where_wide_ones_save_no_pass(n):
+    # one high X mask: one pass in frames of any size
+    M = 60
+    x, z, phi = synth.random_pauli_rotations(n, M, seed=n)
+    x = (x & np.uint64(0x7f)) | np.uint64(1 << (n - 1))
+    s = P.prx_sched_from_rotations(n, x, z, phi / 8)
+    pl = P.prx_plan_create(s, n, P.PRX_C64, 0, M, P.PRX_FUSED)
+    info = P.prx_plan_get_info(pl)
+    assert info["tile_qubits"] == 12 and info["passes"] == 1
+    P.prx_plan_destroy(pl)
+    P.prx_sched_destroy(s)
