@@ -644,7 +644,12 @@ void tile_args(int n, prx_dtype dtype, const Pass &ps, TileArgs &a) {
     a.n = n;
     a.b = ps.b;
     a.g = ps.g;
-    a.stream = streams_state(std::ldexp(dtype == PRX_C64 ? 8.0 : 16.0, n));
+    // (tile passes stream up to 64 MiB, twice the L2s: ordinary / non-temporal
+    // us, 22 qubits complex128 qDRIFT 453 / 429, second-order step 775 / 748; 100
+    // rotations in one pass of 23 qubits complex64 98 / 90.  Span passes and
+    // sweeps between them keep the 32 MiB: 512 / 567 with theirs at 64)
+    const double bytes = std::ldexp(dtype == PRX_C64 ? 8.0 : 16.0, n);
+    a.stream = streams_state(bytes) || bytes <= 64.0 * 1048576.0;
     a.chunk_begin = (uint32_t)ps.c0;
     a.chunk_count = (uint32_t)(ps.c1 - ps.c0);
     a.scale = ps.scale;
