@@ -919,6 +919,7 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         // a state that one workgroup's LDS holds, unless the caller asked for
         // particular frames
         if (fused && !internal && !P->cfg.shaped) default_frames(dtype, n, P->cfg);
+        if (!internal) P->cfg.narrow = P->cfg.tile_only;
         const PlanCfg tiled = P->cfg;
         if (fused && !internal && !P->cfg.shaped && n >= kResidentMinQubits &&
             n <= resident_max_qubits(dtype)) {
@@ -928,7 +929,6 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             P->cfg.max_fuse = std::min(P->cfg.max_fuse, 128);
             P->cfg.commuting = P->cfg.relabel = false;  // every rotation fits already
         }
-        if (!internal) P->cfg.narrow = P->cfg.tile_only;
         if (internal) P->resident = internal->resident;
         if (P->cfg.tile_only && (!fused || n < P->cfg.B)) {
             delete P;

@@ -68,3 +68,26 @@ def test_narrow_frames_where_wide_ones_save_no_pass(n):
     assert info["tile_qubits"] == 12 and info["passes"] == 1
     P.prx_plan_destroy(pl)
     P.prx_sched_destroy(s)
+
+
+@pytest.mark.parametrize("dirs", [5, 6, 7])
+@pytest.mark.parametrize("n,dtype,B", [(14, P.PRX_C64, 12), (13, P.PRX_C128, 11),
+                                       (12, P.PRX_C128, 11)])
+def test_plans_too_slow_in_lds_take_the_frames_they_were_compared_with(n, dtype, B, dirs):
+    """A state that one workgroup's LDS holds takes tile passes where few of
+    them do; those are the frames of B - 4 masks that the rule counted, not
+    frames of n - B."""
+    M = 480
+    x, z, phi = synth.random_pauli_rotations(n, M, seed=n + dirs)
+    x &= np.uint64(((1 << dirs) - 1) << (n - dirs) | 15)
+    s = P.prx_sched_from_rotations(n, x, z, phi / 8)
+    named = P.prx_plan_create(s, n, dtype, 0, M, P.PRX_FUSED,
+                              dict(tile_qubits=B, max_virtual=B - 4))
+    fewest = P.prx_plan_get_info(named)["passes"]
+    P.prx_plan_destroy(named)
+    assert fewest == 4
+    pl = P.prx_plan_create(s, n, dtype, 0, M, P.PRX_FUSED)
+    info = P.prx_plan_get_info(pl)
+    assert info["tile_qubits"] == B and info["passes"] == fewest
+    P.prx_plan_destroy(pl)
+    P.prx_sched_destroy(s)
