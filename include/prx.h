@@ -299,7 +299,9 @@ prx_status prx_plan_rotation(const prx_plan *plan, size_t i, prx_rot_info *out);
 /* One-call application and reductions.                                */
 /* ------------------------------------------------------------------ */
 
-/* Workspace bytes prx_apply_range needs for the whole schedule. */
+/* Workspace bytes that are enough for prx_apply_range over any range of the
+ * schedule (a range's own plan, prx_plan_info.workspace_bytes, often takes
+ * less). */
 size_t prx_workspace_bytes(int n, prx_dtype dtype, const prx_sched *sched, prx_kernel kernel);
 
 /* Plans, uploads and executes rotations [begin, end) on psi, then waits
@@ -316,9 +318,8 @@ prx_status prx_apply_range(void *psi, int n, prx_dtype dtype, const prx_sched *s
  * place of a caller workspace.  The call allocates no device memory.
  *   psi    device, 2^n contiguous elements of dtype, updated in place;
  *   stream hipStream_t (NULL = default stream); the call waits for it.
- * INVALID when the plan's workspace (prx_plan_info.workspace_bytes, as
- * prx_workspace_bytes reports for the same range) exceeds the buffer,
- * before any device work; otherwise as prx_apply_range.  Every call on one
+ * INVALID when the plan's workspace (prx_plan_info.workspace_bytes) exceeds
+ * the buffer, before any device work; otherwise as prx_apply_range.  Every call on one
  * GPU uses that GPU's one buffer: the library serialises its own calls with
  * a lock, and work that overlaps a call on the same GPU through any other
  * path that uses the buffer would race.  Nothing in the buffer needs to

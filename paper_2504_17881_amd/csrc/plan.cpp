@@ -891,15 +891,94 @@ static void pack_chunks(prx_plan &P) {
     }
 }
 
-static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtype, size_t begin,
-                                   size_t end, prx_kernel kernel, const prx_plan_opts *opts,
-                                   const PlanCfg *internal, prx_plan **out) {
-    if (!sched || !out) return fail(PRX_ERR_INVALID, "null pointer");
+static prx_status check_plan_args(const prx_sched *sched, int n, prx_dtype dtype,
+                                  prx_kernel kernel) {
     if (dtype != PRX_C64 && dtype != PRX_C128) return fail(PRX_ERR_INVALID, "bad dtype");
     if (kernel < PRX_PLAIN || kernel > PRX_AUTO) return fail(PRX_ERR_INVALID, "bad kernel");
     if (n != sched->n) return fail(PRX_ERR_INVALID, "n differs from the schedule's n");
     if (n < 1) return fail(PRX_ERR_INVALID, "n must be >= 1");
     if (n > 40) return fail(PRX_ERR_UNSUPPORTED, "n > 40 does not fit one device");
+    return PRX_OK;
+}
+
+// The settings a plan starts from: defaults, the tuned entry (AUTO), options.
+static void caller_cfg(int n, prx_dtype dtype, prx_kernel kernel, const prx_plan_opts *opts,
+                       PlanCfg &c) {
+    default_cfg(dtype, c);
+    if (kernel == PRX_AUTO) {
+        prx_plan_opts t;
+        if (tune_lookup(n, dtype, &t)) apply_opts(&t, c);
+    }
+    apply_opts(opts, c);
+    if (kernel != PRX_PLAIN && !c.shaped) default_frames(dtype, n, c);
+    c.narrow = c.tile_only;
+}
+
+// Settings that a fused plan cannot take.
+static prx_status check_cfg(const PlanCfg &c, int n, prx_dtype dtype) {
+    if (!tile_supported(dtype, c.B, c.m) && (n > c.B || c.tile_only))
+        return fail(PRX_ERR_UNSUPPORTED, "tile shape (tile_qubits, chunk_rank) not built");
+    if (!span_supported(dtype, c.span_m) || c.max_virtual > kMaxVirtual || c.max_fuse < 1 ||
+        c.max_fuse > 4096)
+        return fail(PRX_ERR_INVALID, "bad planner option");
+    return PRX_OK;
+}
+
+// Fused plans apply a rotation in k equal pieces, exp(i phi P) =
+// exp(i (phi/k) P)^k, with k the least integer giving |tan(phi/k)| <=
+// 1/sqrt(2): the pair update's kappa then stays in [1/2, 3/2] and
+// every cosine is at least 0.8 in magnitude.
+static int pieces_of(double phi) {
+    const double tmax = 0.70710678118654752, amax = 0.61547970867038734;  // atan(tmax)
+    return std::fabs(std::tan(phi)) <= tmax ? 1 : (int)std::ceil(std::fabs(phi) / amax);
+}
+
+// Workspace of a plan with these tables, at most `parts` norm partials per
+// hand-off, and hand-offs of up to `direct` summed by the next pass.
+static WsLayout ws_layout(size_t rot_bytes, size_t chunk_bytes, size_t parts, unsigned direct) {
+    WsLayout w;
+    w.rot_bytes = rot_bytes;
+    w.chunk_off = align256(w.rot_off + w.rot_bytes + kRecordReadAhead);
+    w.chunk_bytes = chunk_bytes;
+    w.part_off = align256(w.chunk_off + w.chunk_bytes);
+    w.direct = direct;
+    w.part_bytes = std::max<size_t>(parts, 2 * (size_t)direct) * sizeof(double);
+    w.scal_off = align256(w.part_off + w.part_bytes);
+    w.scal_bytes = (1 + kRenormStage) * sizeof(double);
+    w.total = align256(w.scal_off + w.scal_bytes);
+    return w;
+}
+
+// Workspace that the plan of any part of a schedule fits, whatever frames the
+// part's own rotations lead to.
+//   Records: one per piece.  Norm partials: a span of rank 1 has the most blocks
+//   (2^(n-9), a tile pass at most 2^(n-10)).
+//   Chunks hold at least one rotation.  Under the default options a chunk that
+//   is not the last of its pass holds two (it ends with a full basis or at a
+//   mask that two of its own make up), and R rotations take at most ceil(R / 7)
+//   passes: any seven fit a frame, which holds seven masks or more, and the
+//   planner finds the fewest passes.  So R / 2 + ceil(R / 7) / 2 chunks are
+//   enough, fewer than 5 R / 8 + 1.
+static size_t any_range_bytes(const prx_sched &S, prx_dtype dtype, const PlanCfg &c, bool fused) {
+    size_t R = 0, chunks = 0, blocks = 1;
+    for (double phi : S.phi) R += fused ? (size_t)std::max(0, pieces_of(phi)) : 1;
+    if (fused && S.n >= 4) {
+        chunks = c.shaped || c.relabel || c.max_fuse < 7 ? R : 5 * R / 8 + 1;
+        if (dtype == PRX_C64 && c.renorm_every > 0) blocks = span_blocks(S.n, 1, c.grid_cap);
+    }
+    const bool c64 = dtype == PRX_C64;
+    return ws_layout(R * (c64 ? sizeof(RotRec<float>) : sizeof(RotRec<double>)),
+                     chunks * (c64 ? sizeof(ChunkRec<float>) : sizeof(ChunkRec<double>)), blocks,
+                     (unsigned)std::min<size_t>(blocks, kRenormDirect))
+        .total;
+}
+
+static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtype, size_t begin,
+                                   size_t end, prx_kernel kernel, const prx_plan_opts *opts,
+                                   const PlanCfg *internal, prx_plan **out) {
+    if (!sched || !out) return fail(PRX_ERR_INVALID, "null pointer");
+    prx_status st = check_plan_args(sched, n, dtype, kernel);
+    if (st != PRX_OK) return st;
     if (begin > end || end > sched->x.size()) return fail(PRX_ERR_INVALID, "bad rotation range");
     prx_plan *P = new (std::nothrow) prx_plan;
     if (!P) return fail(PRX_ERR_OOM, "out of host memory");
@@ -908,19 +987,12 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         P->dtype = dtype;
         P->kernel = kernel;
         P->begin = 0;
-        default_cfg(dtype, P->cfg);
-        if (kernel == PRX_AUTO) {
-            prx_plan_opts t;
-            if (tune_lookup(n, dtype, &t)) apply_opts(&t, P->cfg);
-        }
-        apply_opts(opts, P->cfg);
+        caller_cfg(n, dtype, kernel, opts, P->cfg);
         if (internal) P->cfg = *internal;
         const bool fused = kernel != PRX_PLAIN;
+        const PlanCfg tiled = P->cfg;
         // a state that one workgroup's LDS holds, unless the caller asked for
         // particular frames
-        if (fused && !internal && !P->cfg.shaped) default_frames(dtype, n, P->cfg);
-        if (!internal) P->cfg.narrow = P->cfg.tile_only;
-        const PlanCfg tiled = P->cfg;
         if (fused && !internal && !P->cfg.shaped && n >= kResidentMinQubits &&
             n <= resident_max_qubits(dtype)) {
             P->resident = true;
@@ -935,28 +1007,16 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             return fail(PRX_ERR_INVALID, "tile_only needs a fused kernel and n >= tile_qubits");
         }
         if (fused) {
-            if (!tile_supported(dtype, P->cfg.B, P->cfg.m) &&
-                (P->n > P->cfg.B || P->cfg.tile_only)) {
+            st = check_cfg(P->cfg, n, dtype);
+            if (st != PRX_OK) {
                 delete P;
-                return fail(PRX_ERR_UNSUPPORTED, "tile shape (tile_qubits, chunk_rank) not built");
-            }
-            if (!span_supported(dtype, P->cfg.span_m) || P->cfg.max_virtual > kMaxVirtual ||
-                P->cfg.max_fuse < 1 || P->cfg.max_fuse > 4096) {
-                delete P;
-                return fail(PRX_ERR_INVALID, "bad planner option");
+                return st;
             }
         }
-        // Fused plans apply a rotation in k equal pieces, exp(i phi P) =
-        // exp(i (phi/k) P)^k, with k the least integer giving |tan(phi/k)| <=
-        // 1/sqrt(2): the pair update's kappa then stays in [1/2, 3/2] and
-        // every cosine is at least 0.8 in magnitude.
         P->rots.reserve(end - begin);
-        const double tmax = 0.70710678118654752, amax = 0.61547970867038734;  // atan(tmax)
         for (size_t j = begin; j < end; ++j) {
             const double phi = sched->phi[j];
-            int pieces = 1;
-            if (fused && !(std::fabs(std::tan(phi)) <= tmax))
-                pieces = (int)std::ceil(std::fabs(phi) / amax);
+            const int pieces = fused ? pieces_of(phi) : 1;
             const double part = phi / pieces;
             for (int q = 0; q < pieces; ++q) P->rots.push_back(KRot{sched->x[j], sched->z[j], part, j});
         }
@@ -1091,25 +1151,11 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
                                                : tile_blocks(n, ps.B, P->cfg.grid_cap);
             maxblocks = std::max(maxblocks, nb);
         }
-        WsLayout &w = P->ws;
-        w.rot_off = 0;
-        w.rot_bytes = P->rot_table.size();
-        w.chunk_off = align256(w.rot_off + w.rot_bytes + kRecordReadAhead);
-        w.chunk_bytes = P->chunk_table.size();
-        w.part_off = align256(w.chunk_off + w.chunk_bytes);
-        w.scal_bytes = (1 + kRenormStage) * sizeof(double);
-        w.direct = (unsigned)std::min<size_t>(maxblocks, kRenormDirect);
-        auto place = [&](size_t parts) {
-            w.part_bytes = parts * sizeof(double);
-            w.scal_off = align256(w.part_off + w.part_bytes);
-            w.total = align256(w.scal_off + w.scal_bytes);
-        };
-        place(std::max<size_t>(maxblocks, 2 * w.direct));
-        if (w.total > PRX_STATIC_WS_BYTES) {
-            // a plan at the edge of the static buffer keeps the one region
-            w.direct = 0;
-            place(maxblocks);
-        }
+        P->ws = ws_layout(P->rot_table.size(), P->chunk_table.size(), maxblocks,
+                          (unsigned)std::min<size_t>(maxblocks, kRenormDirect));
+        // a plan at the edge of the static buffer keeps the one region
+        if (P->ws.total > PRX_STATIC_WS_BYTES)
+            P->ws = ws_layout(P->rot_table.size(), P->chunk_table.size(), maxblocks, 0);
     } catch (const std::bad_alloc &) {
         delete P;
         return fail(PRX_ERR_OOM, "out of host memory");
@@ -1429,13 +1475,12 @@ prx_status prx_plan_rotation(const prx_plan *P, size_t i, prx_rot_info *o) {
 }
 
 size_t prx_workspace_bytes(int n, prx_dtype dtype, const prx_sched *sched, prx_kernel kernel) {
-    if (!sched) return 0;
-    prx_plan *P = nullptr;
-    if (prx_plan_create(sched, n, dtype, 0, sched->x.size(), kernel, nullptr, &P) != PRX_OK)
-        return 0;
-    const size_t b = P->ws.total;
-    prx_plan_destroy(P);
-    return b;
+    if (!sched || check_plan_args(sched, n, dtype, kernel) != PRX_OK) return 0;
+    PlanCfg c;
+    caller_cfg(n, dtype, kernel, nullptr, c);
+    const bool fused = kernel != PRX_PLAIN;
+    if (fused && check_cfg(c, n, dtype) != PRX_OK) return 0;
+    return any_range_bytes(*sched, dtype, c, fused);
 }
 
 prx_status prx_apply_range(void *psi, int n, prx_dtype dtype, const prx_sched *sched,
