@@ -990,6 +990,18 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
         caller_cfg(n, dtype, kernel, opts, P->cfg);
         if (internal) P->cfg = *internal;
         const bool fused = kernel != PRX_PLAIN;
+        if (P->cfg.tile_only && (!fused || n < P->cfg.B)) {
+            delete P;
+            return fail(PRX_ERR_INVALID, "tile_only needs a fused kernel and n >= tile_qubits");
+        }
+        if (fused) {
+            // (before a resident plan limits max_fuse itself)
+            st = check_cfg(P->cfg, n, dtype);
+            if (st != PRX_OK) {
+                delete P;
+                return st;
+            }
+        }
         const PlanCfg tiled = P->cfg;
         // a state that one workgroup's LDS holds, unless the caller asked for
         // particular frames
@@ -1002,17 +1014,6 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             P->cfg.commuting = P->cfg.relabel = false;  // every rotation fits already
         }
         if (internal) P->resident = internal->resident;
-        if (P->cfg.tile_only && (!fused || n < P->cfg.B)) {
-            delete P;
-            return fail(PRX_ERR_INVALID, "tile_only needs a fused kernel and n >= tile_qubits");
-        }
-        if (fused) {
-            st = check_cfg(P->cfg, n, dtype);
-            if (st != PRX_OK) {
-                delete P;
-                return st;
-            }
-        }
         P->rots.reserve(end - begin);
         for (size_t j = begin; j < end; ++j) {
             const double phi = sched->phi[j];
