@@ -318,9 +318,10 @@ prx_status prx_apply_range(void *psi, int n, prx_dtype dtype, const prx_sched *s
  * place of a caller workspace.  The call allocates no device memory.
  *   psi    device, 2^n contiguous elements of dtype, updated in place;
  *   stream hipStream_t (NULL = default stream); the call waits for it.
- * INVALID when the plan's workspace (prx_plan_info.workspace_bytes) exceeds
- * the buffer, before any device work; otherwise as prx_apply_range.  Every call on one
- * GPU uses that GPU's one buffer: the library serialises its own calls with
+ * A range whose default plan exceeds the buffer takes the plan with the
+ * smallest tables, mostly span passes; INVALID when that exceeds it too,
+ * before any device work; otherwise as prx_apply_range.  Every call on one GPU
+ * uses that GPU's one buffer: the library serialises its own calls with
  * a lock, and work that overlaps a call on the same GPU through any other
  * path that uses the buffer would race.  Nothing in the buffer needs to
  * start at zero: each call writes every byte it later reads. */

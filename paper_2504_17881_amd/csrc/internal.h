@@ -220,9 +220,13 @@ bool tune_lookup(int n, prx_dtype dt, prx_plan_opts *out);
 void tune_store(int n, prx_dtype dt, const prx_plan_opts &o);
 
 struct PlanCfg;
-// Plan with explicit internal settings (batched plans: span-only, fixed rank).
+// Plan with explicit internal settings (batched plans).
 prx_status plan_create_cfg(const prx_sched *sched, int n, prx_dtype dtype, const PlanCfg &cfg,
                            prx_plan **out);
+// Plan of a range whose default plan's tables are too large: span passes, which
+// have no chunk records, wherever a frame of n - B masks covers no more.
+prx_status plan_create_small(const prx_sched *sched, int n, prx_dtype dtype, size_t begin,
+                             size_t end, prx_kernel kernel, prx_plan **out);
 
 // ------------------------------------------------------------ launchers
 // All enqueue on `stream` and return hipGetLastError() of the launch.

@@ -1174,6 +1174,20 @@ prx_status plan_create_cfg(const prx_sched *sched, int n, prx_dtype dtype, const
                             &cfg, out);
 }
 
+prx_status plan_create_small(const prx_sched *sched, int n, prx_dtype dtype, size_t begin,
+                             size_t end, prx_kernel kernel, prx_plan **out) {
+    PlanCfg c;
+    caller_cfg(n, dtype, kernel, nullptr, c);
+    if (!c.shaped) {
+        PlanCfg d;
+        default_cfg(dtype, d);
+        c.B = d.B;
+        c.max_virtual = d.max_virtual;
+    }
+    c.narrow = true;
+    return plan_create_impl(sched, n, dtype, begin, end, kernel, nullptr, &c, out);
+}
+
 }  // namespace prx
 
 extern "C" {
