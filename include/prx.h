@@ -335,7 +335,8 @@ size_t prx_reduce_workspace_bytes(int n);
 /* out_re_im = <psi0|psi> = sum_k conj(psi0[k]) psi[k] (Methods, "Data
  * analysis", the signal g(t)), accumulated in FP64 with compensated
  * per-thread sums and a fixed-shape tree (deterministic).  Synchronises
- * the stream. */
+ * the stream.  The first reduction of a process allocates one page of pinned
+ * host memory for results. */
 prx_status prx_overlap(const void *psi0, const void *psi, int n, prx_dtype dtype,
                        double out_re_im[2], void *ws, size_t ws_bytes, void *stream);
 
