@@ -375,18 +375,20 @@ typedef struct prx_graph prx_graph;
 prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sched,
                             prx_dtype dtype, const uint64_t *basis_idx, prx_batch **out);
 size_t prx_batch_workspace_bytes(const prx_batch *b);
-/* Summary of a batch plan. */
+/* Summary of a batch as pass counts.  A sample of 12 (complex128: 11) to 14
+ * qubits counts the passes of a tile_only plan of 12 (11) tile qubits with
+ * commuting on, a measure of its sequence rather than of its launches: it runs
+ * in one launch in LDS, or at 14 qubits complex128 in fewer passes of wider
+ * frames.  prx_batch_get_info makes those plans; the batch holds copies of
+ * their rotations for it. */
 typedef struct {
     size_t samples;       /* S */
     size_t tile_samples;  /* samples of at least 12 qubits (complex128: 11) */
     size_t rounds;        /* largest pass count */
-    size_t passes;        /* passes summed over the samples; a sample of 12 (11) to 14
-                             qubits counts the passes of a tile_only plan of 12 (11)
-                             tile qubits with commuting on */
-    double amp_sweeps;    /* sum over samples of passes * 2^n: each sweep reads and
-                             writes every amplitude once (algorithmic bytes
-                             = 2 * amp_sweeps * bytes per amplitude; a sample that
-                             stays in LDS makes its sweeps there) */
+    size_t passes;        /* passes summed over the samples */
+    double amp_sweeps;    /* sum over samples of passes * 2^n; a sweep of a sample of
+                             15 or more qubits reads and writes every amplitude once
+                             (algorithmic bytes = 2 * amp_sweeps * bytes per amplitude) */
 } prx_batch_info;
 prx_status prx_batch_get_info(const prx_batch *b, prx_batch_info *out);
 /* Records the device state pointers psi[s] (host array of S distinct,

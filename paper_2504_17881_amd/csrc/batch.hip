@@ -259,7 +259,8 @@ struct prx_batch {
     };
     std::vector<Round> rounds;
     int B = 12;                             // their tile qubits
-    prx_batch_info info = {};
+    prx_batch_info info = {};               // without the samples of `counted`
+    std::vector<prx_sched> counted;         // those whose passes prx_batch_get_info counts
     unsigned max_grid = 0;  // 0: the default grid caps
     // workspace layout
     size_t off_samples = 0, off_residents = 0, off_tpasses = 0, off_tfirst = 0, off_chunks = 0,
@@ -286,6 +287,27 @@ static uint32_t append_tables(prx_batch *b, const prx_plan *P, size_t csz, size_
         reinterpret_cast<ChunkHead *>(b->chunks.data() + c)->rot_begin += rot_base;
     b->rots.insert(b->rots.end(), P->rot_table.begin(), P->rot_table.end());
     return (uint32_t)(at / csz);
+}
+
+// Plans of tile passes only; the caller sets the frames.
+static PlanCfg tile_settings() {
+    PlanCfg c;
+    c.tile_only = true;
+    c.narrow = false;
+    c.m = kBatchTileM;
+    c.renorm_every = -1;
+    c.max_fuse = 128;
+    // exact reorders: a later rotation that fits the pass's frame and
+    // commutes with every rotation it passes joins the pass (10-20 %
+    // fewer passes on random-order qDRIFT sequences)
+    c.commuting = true;
+    return c;
+}
+
+static void count_passes(prx_batch_info &info, size_t passes, int n) {
+    info.passes += passes;
+    info.rounds = std::max(info.rounds, passes);
+    info.amp_sweeps += (double)passes * std::ldexp(1.0, n);
 }
 
 // A sample's tile passes before they are laid out by rounds.
@@ -420,15 +442,7 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
         res_cfg.renorm_every = -1;
         res_cfg.max_fuse = 128;
         res_cfg.commuting = true;
-        PlanCfg tile_cfg;
-        tile_cfg.tile_only = true;
-        tile_cfg.m = kBatchTileM;
-        tile_cfg.renorm_every = -1;
-        tile_cfg.max_fuse = 128;
-        // exact reorders: a later rotation that fits the pass's frame and
-        // commutes with every rotation it passes joins the pass (10-20 %
-        // fewer passes on random-order qDRIFT sequences)
-        tile_cfg.commuting = true;
+        PlanCfg tile_cfg = tile_settings();
         double amps = 0.0;
         int fewest = 64;
         for (size_t s = 0; s < S; ++s)
@@ -445,22 +459,8 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
             size_t passes = 0;
             prx_plan *P = nullptr;
             if (n[s] >= TB) ++b->info.tile_samples;
-            if (n[s] >= TB && n[s] <= 14) {
-                // samples up to two qubits above the tile size report the
-                // passes of narrow frames, whatever they run
-                tile_cfg.narrow = true;
-                tile_cfg.B = TB;
-                tile_cfg.max_virtual = TB - kMinTileLow;
-                prx_status st = plan_create_cfg(sched[s], n[s], dtype, tile_cfg, &P);
-                if (st != PRX_OK) {
-                    delete b;
-                    return st;
-                }
-                passes = P->passes.size();
-                prx_plan_destroy(P);
-            }
+            if (n[s] >= TB && n[s] <= 14) b->counted.push_back(*sched[s]);
             if (!resident) {
-                tile_cfg.narrow = false;
                 tile_cfg.B = b->B;
                 tile_cfg.max_virtual = b->B - kMinTileLow;
                 prx_status st = plan_create_cfg(sched[s], n[s], dtype, tile_cfg, &P);
@@ -507,9 +507,7 @@ prx_status prx_batch_create(size_t S, const int *n, const prx_sched *const *sche
                 }
                 prx_plan_destroy(P);
             }
-            b->info.passes += passes;
-            b->info.rounds = std::max(b->info.rounds, passes);
-            b->info.amp_sweeps += (double)passes * std::ldexp(1.0, n[s]);
+            count_passes(b->info, passes, n[s]);
         }
         make_launches(b);
         make_rounds(b, tiles);
@@ -533,7 +531,21 @@ size_t prx_batch_workspace_bytes(const prx_batch *b) { return b ? b->total : 0; 
 
 prx_status prx_batch_get_info(const prx_batch *b, prx_batch_info *out) {
     if (!b || !out) return fail(PRX_ERR_INVALID, "null pointer");
-    *out = b->info;
+    prx_batch_info info = b->info;
+    // samples up to two qubits above the tile size report the passes of narrow
+    // frames, whatever they run: planned here, where they are asked for
+    PlanCfg c = tile_settings();
+    c.narrow = true;
+    c.B = batch_tile_qubits(b->dtype);
+    c.max_virtual = c.B - kMinTileLow;
+    for (const prx_sched &s : b->counted) {
+        prx_plan *P = nullptr;
+        const prx_status st = plan_create_cfg(&s, s.n, b->dtype, c, &P);
+        if (st != PRX_OK) return st;
+        count_passes(info, P->passes.size(), s.n);
+        prx_plan_destroy(P);
+    }
+    *out = info;
     return PRX_OK;
 }
 
