@@ -852,17 +852,21 @@ static void apply_opts(const prx_plan_opts *o, PlanCfg &c) {
         c.grid_cap = (unsigned)std::min<uint64_t>((uint64_t)o->max_grid, kMaxGridBlocks);
 }
 
-// The threaded rotation loop of the complex64 tile chunks reads one record
-// with one 32-byte scalar load: z, zhigh, info, pad, tau_a, tau_b.
-static_assert(sizeof(RotRec<float>) == 32 && offsetof(RotRec<float>, zhigh) == 8 &&
-                  offsetof(RotRec<float>, info) == 16 && offsetof(RotRec<float>, tau_a) == 24 &&
+// The rotation loops of complex64 chunks read one record with one 32-byte
+// scalar load: z, zhigh, info, jump, tau_a, tau_b; the lean ones branch to the
+// address that `jump` names.
+static_assert(sizeof(RotRec<float>) == 32 && offsetof(RotRec<float>, z) == 0 &&
+                  offsetof(RotRec<float>, zhigh) == 8 && offsetof(RotRec<float>, info) == 16 &&
+                  offsetof(RotRec<float>, jump) == 20 && offsetof(RotRec<float>, tau_a) == 24 &&
                   offsetof(RotRec<float>, tau_b) == 28,
-              "record layout read by the threaded rotation loop");
-// The complex128 loop reads 32 bytes (z, zhigh, info, pad, tau_a) and then
+              "record layout read by the rotation loops");
+// The complex128 loops read 32 bytes (z, zhigh, info, jump, tau_a) and then
 // tau_b at byte 32.
-static_assert(sizeof(RotRec<double>) == 40 && offsetof(RotRec<double>, info) == 16 &&
-                  offsetof(RotRec<double>, tau_a) == 24 && offsetof(RotRec<double>, tau_b) == 32,
-              "record layout read by the complex128 threaded rotation loop");
+static_assert(sizeof(RotRec<double>) == 40 && offsetof(RotRec<double>, z) == 0 &&
+                  offsetof(RotRec<double>, zhigh) == 8 && offsetof(RotRec<double>, info) == 16 &&
+                  offsetof(RotRec<double>, jump) == 20 && offsetof(RotRec<double>, tau_a) == 24 &&
+                  offsetof(RotRec<double>, tau_b) == 32,
+              "record layout read by the complex128 rotation loops");
 
 template <typename T>
 static void pack_records(prx_plan &P, const std::vector<RotRecD> &recs) {
