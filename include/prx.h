@@ -153,7 +153,9 @@ typedef struct {
     int max_virtual;     /* max high-qubit XOR masks gathered into a tile, <= 10; the tile
                             keeps at least 16 contiguous amplitudes (default 8; where no
                             tile or span option is given, tile_qubits - 4) */
-    int renorm_every;    /* C64: renormalise in FP64 every k passes (default 1; -1 = never) */
+    int renorm_every;    /* C64: renormalise in FP64 every k passes (default 1; -1 = never):
+                            between passes over the state, and before the last chunk of a
+                            resident plan; any other plan of one pass is not renormalised */
     int commuting;       /* 1: planner may swap adjacent commuting rotations (default 0) */
     int tile_only;       /* 1: every pass a tile pass, as batched samples of >= tile_qubits
                             qubits are planned (default 0); INVALID with PRX_PLAIN or

@@ -116,8 +116,8 @@ struct ChunkRec {
 static_assert(sizeof(ChunkHead) == 64 && sizeof(ChunkRec<float>) == 192 &&
               sizeof(ChunkRec<double>) == 320, "whole cache lines");
 static constexpr uint32_t kChunkPassEnd = 1;   // last chunk of a pass: its scale applies here,
-static constexpr uint32_t kChunkRenormIn = 2;  // times the renormalisation factor in force;
-static constexpr uint32_t kChunkNormOut = 4;   // and the norm after it makes the next factor
+static constexpr uint32_t kChunkRenormIn = 2;  // times the renormalisation factor in force
+static constexpr uint32_t kChunkNormOut = 4;   // the norm after a chunk makes the next factor
 
 // Longest run of rotations in one chunk (bounds the pending factors: with
 // tau^2 <= 1/2 each kappa lies in [1/2, 3/2]).

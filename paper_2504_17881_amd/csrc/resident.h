@@ -183,10 +183,10 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
                 if (ch.flags & kChunkPassEnd) {
                     o.re *= s;
                     o.im *= s;
-                    if constexpr (kRenorm<T>) {
-                        nrm = fma((double)o.re, (double)o.re, nrm);
-                        nrm = fma((double)o.im, (double)o.im, nrm);
-                    }
+                }
+                if (kRenorm<T> && (ch.flags & kChunkNormOut)) {
+                    nrm = fma((double)o.re, (double)o.re, nrm);
+                    nrm = fma((double)o.im, (double)o.im, nrm);
                 }
                 *reinterpret_cast<Cx<T> *>(lds_raw + (k0b ^ Xb[v])) = o;
             }
