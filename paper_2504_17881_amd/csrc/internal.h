@@ -102,11 +102,13 @@ struct ChunkHead {
     uint32_t flags;  // resident plans: kChunk* bits
     uint32_t basis[kMaxChunkRank];
     uint16_t cvec[kMaxTileThreadBits];
-    double scale;    // resident plans, at a pass's last chunk: the pass's scale
+    double scale;    // resident plans, complex128: at a pass's last chunk its scale;
+                     // complex64: what the factors' roundings leave on average
 };
 // The device record, in cache lines: the head, then the factors of the coset
 // labels in the state's precision (label v's pending factor, the product of
-// the chunk's per-slot factors K over the bits set in v; v < 2^m, m <= 5).  A
+// the chunk's per-slot factors K over the bits set in v; v < 2^m, m <= 5; in
+// resident complex64 plans times the cosines of the chunk's rotations).  A
 // rank-4 complex64 chunk reads two lines.
 template <typename T>
 struct ChunkRec {
@@ -115,9 +117,9 @@ struct ChunkRec {
 };
 static_assert(sizeof(ChunkHead) == 64 && sizeof(ChunkRec<float>) == 192 &&
               sizeof(ChunkRec<double>) == 320, "whole cache lines");
-static constexpr uint32_t kChunkPassEnd = 1;   // last chunk of a pass: its scale applies here,
-static constexpr uint32_t kChunkRenormIn = 2;  // times the renormalisation factor in force
-static constexpr uint32_t kChunkNormOut = 4;   // the norm after a chunk makes the next factor
+static constexpr uint32_t kChunkPassEnd = 1;   // last chunk of a pass: takes its scale (complex128)
+static constexpr uint32_t kChunkRenormIn = 2;  // takes the renormalisation factor in force
+static constexpr uint32_t kChunkNormOut = 4;   // the norm after it makes the next factor
 
 // Longest run of rotations in one chunk (bounds the pending factors: with
 // tau^2 <= 1/2 each kappa lies in [1/2, 3/2]).

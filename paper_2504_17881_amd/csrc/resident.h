@@ -104,7 +104,10 @@ __device__ __forceinline__ double inv_sqrt(double v) {
 // pass.  The frame is the global index, so every rotation fits it and a chunk
 // ends only when its basis is full.  Bound by the latency of a chunk's chain
 // (gather, rotations, scatter, barrier) up to 12 qubits, where a SIMD holds
-// one wave, and by one CU's vector ALU and LDS at 14.
+// one wave, and by one CU's vector ALU and LDS at 14.  What only some chunks
+// do stands in branches of its own (100 rotations of 10 qubits complex64 28.1
+// us with selects in every chunk and 25.4 so, 300 of 14 qubits 132 and 124; a
+// sample of 13 qubits complex128, 200 rotations, 104 and 89).
 template <typename T, int B>
 struct ResidentShape {
     static constexpr int M = 4;
@@ -169,27 +172,44 @@ __device__ __forceinline__ void resident_run(Cx<T> *lds, double (*red)[16], Cx<T
             for (int v = 0; v < PER; ++v)
                 amp[v] = *reinterpret_cast<const Cx<T> *>(lds_raw + (k0b ^ Xb[v]));
             apply_chunk<T, kRotLean>(amp, k0, 0, rots + ch.rot_begin, ch.rot_count);
-            double sc = ch.scale;
-            if (kRenorm<T> && (ch.flags & kChunkRenormIn)) sc *= rn;
-            const T s = (T)sc;
-            double nrm = 0.0;
+            // complex64 factors hold the chunk's cosines too, complex128 ones
+            // leave label 0 as it is
 #pragma unroll
-            for (int v = 0; v < PER; ++v) {
-                Cx<T> o = amp[v];
-                if (v) {  // (label 0 has no pending factor)
-                    o.re *= rec.fac[v];
-                    o.im *= rec.fac[v];
-                }
-                if (ch.flags & kChunkPassEnd) {
-                    o.re *= s;
-                    o.im *= s;
-                }
-                if (kRenorm<T> && (ch.flags & kChunkNormOut)) {
-                    nrm = fma((double)o.re, (double)o.re, nrm);
-                    nrm = fma((double)o.im, (double)o.im, nrm);
-                }
-                *reinterpret_cast<Cx<T> *>(lds_raw + (k0b ^ Xb[v])) = o;
+            for (int v = kRenorm<T> ? 0 : 1; v < PER; ++v) {
+                amp[v].re *= rec.fac[v];
+                amp[v].im *= rec.fac[v];
             }
+            double nrm = 0.0;
+            if constexpr (kRenorm<T>) {
+                if (ch.flags & kChunkRenormIn) {
+                    // (rounded, a factor near 1 would be off by as much as the
+                    // rotations of a chunk: the rest goes in too)
+                    const double sc = rn * ch.scale;
+                    const T s = (T)sc, s_lo = (T)(sc - (double)s);
+#pragma unroll
+                    for (int v = 0; v < PER; ++v) {
+                        amp[v].re = fma(amp[v].re, s, amp[v].re * s_lo);
+                        amp[v].im = fma(amp[v].im, s, amp[v].im * s_lo);
+                    }
+                }
+                if (ch.flags & kChunkNormOut) {
+#pragma unroll
+                    for (int v = 0; v < PER; ++v) {
+                        nrm = fma((double)amp[v].re, (double)amp[v].re, nrm);
+                        nrm = fma((double)amp[v].im, (double)amp[v].im, nrm);
+                    }
+                }
+            } else if (ch.flags & kChunkPassEnd) {
+                const T s = (T)ch.scale;
+#pragma unroll
+                for (int v = 0; v < PER; ++v) {
+                    amp[v].re *= s;
+                    amp[v].im *= s;
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < PER; ++v)
+                *reinterpret_cast<Cx<T> *>(lds_raw + (k0b ^ Xb[v])) = amp[v];
             if (kRenorm<T> && (ch.flags & kChunkNormOut)) {
                 if (tid >= ncos) nrm = 0.0;
                 nrm = wave_sum(nrm);
