@@ -1198,6 +1198,10 @@ static prx_status plan_create_impl(const prx_sched *sched, int n, prx_dtype dtyp
             if (dtype == PRX_C64 && P->cfg.renorm_every > 0 && nc > 1) {
                 P->chunks[nc - 2].h.flags |= kChunkNormOut;
                 P->chunks[nc - 1].h.flags |= kChunkRenormIn;
+                if (P->passes.back().c0 == nc - 1) {  // (launched pass by pass, through `scal`)
+                    P->passes[P->passes.size() - 2].norm_out = true;
+                    P->passes.back().renorm_in = true;
+                }
             }
             // complex64 chunks hold their own cosines in their factors: products
             // just below 1, which round half as far as the factors above it.  What

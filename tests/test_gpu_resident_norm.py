@@ -38,6 +38,25 @@ def test_norm_of_repeated_plans(n, M, runs):
     P.prx_sched_destroy(s)
 
 
+@pytest.mark.parametrize("every", [1, 2, 3])
+@pytest.mark.parametrize("M", [3, 128, 131, 259])
+def test_timed_form_with_a_last_pass_of_one_chunk(M, every):
+    n = 8
+    x, z, phi = synth.random_pauli_rotations(n, M, seed=5)
+    s = P.prx_sched_from_rotations(n, x, z, phi / 8)
+    pl = P.prx_plan_create(s, n, P.PRX_C64, 0, M, P.PRX_FUSED, dict(renorm_every=every))
+    ws = workspace(P.prx_plan_get_info(pl)["workspace_bytes"])
+    P.prx_plan_upload(pl, ws)
+    a = to_dev(1.5 * synth.gaussian_state(n, 1), P.PRX_C64)
+    b = a.clone()
+    print(f"[timed M={M} every={every}]", flush=True)
+    P.prx_plan_execute(pl, a, ws)
+    P.prx_plan_execute_timed(pl, b, ws)
+    assert np.array_equal(to_host(a), to_host(b))
+    P.prx_plan_destroy(pl)
+    P.prx_sched_destroy(s)
+
+
 def _plain_fp32(n, x, z, phi, psi, ends, fp32):
     """psi + tau sigma psi' rotation by rotation, the cosines at the ends of the
     chunks; in FP32 every result is rounded once.  Normalised at the end."""
