@@ -38,7 +38,9 @@ static int batch_tile_qubits(prx_dtype dt) { return dt == PRX_C64 ? 12 : 11; }
 // Measured (us per batch, 12 / 13 / 14 qubits): 20 samples of 17 qubits 472 /
 // 491 / 636, 20 of 19 1280 / 1182 / 1248, 24 of 23 21456 / 19488 / 20786, 6 of
 // 24 6448 / 5845 / 5479, 4 of 25 8212 / 7609 / 7289; 24 samples of 22 qubits,
-// one 14-qubit set of each per CU, take 12311 with 14 and 8847 with 13.
+// one 14-qubit set of each per CU, take 12311 with 14 and 8847 with 13.  Mixed
+// sizes gain nothing from 14 either: 32 samples of 16 to 22 qubits move 40.0 GB
+// in 8541 us with 13 and 34.3 GB in 8667 with 14.
 // complex128, 32 of 15 to 21: 10773 with 11 qubits, 9539 with 12, 10444 with
 // 13; 64 of 14 to 17 3096 with 11 and 2736 with 12.
 static int batch_frame_qubits(prx_dtype dt, double amps, int fewest) {
@@ -182,9 +184,10 @@ __global__ void __launch_bounds__(1 << (B - M))
         const uint64_t tb =
             ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(set.tb >> 32)) << 32) |
             __builtin_amdgcn_readfirstlane((uint32_t)set.tb);
-        // (rot_loop where the round is bound by its sweeps and the loops differ by
-        // 1 to 2 %: 6 samples of 24 qubits 9.36 ms and 9.20, complex128 8 of 23
-        // 14.38 and 14.35)
+        // (rot_loop where the round is bound by its sweeps and the loops are within
+        // 2 %; the tests of the built code look for instances of it here.  rot_loop /
+        // lean: 6 samples of 24 qubits 10.31 / 10.15 ms, complex128 8 of 23 16.15 /
+        // 16.12, 32 of 15 to 21 4.57 / 4.50)
         constexpr bool swept = PERSIST || (sizeof(T) == 8 && B == 12);
         tile_chunks<T, B, M, swept ? kRotLoop : kRotLeanTile>(lds_raw, tmask, tb, chunks + bp->a.chunk_begin, bp->a.chunk_count,
                              reinterpret_cast<const RotRec<T> *>(rot_table));

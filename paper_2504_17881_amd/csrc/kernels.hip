@@ -228,9 +228,12 @@ __global__ void __launch_bounds__(256) k_span(Cx<T> *__restrict__ psi, SpanArgs 
 // The rotation loop of a shape.  The lean one takes 300-rotation sequences at
 // 15 qubits complex64 from 115 to 103 us (sorted) and 180 to 169 (qDRIFT), at
 // 16 qubits complex128 from 130 to 122, a fifth of the 32-qubit step from 820
-// to 810 ms.  Where several small workgroups share a SIMD the two differ by 0
-// to 2 %; the 10-qubit shape, which no default frame uses, keeps rot_loop (the
-// one whose layout is checked with the jump tables).
+// to 810 ms.  The 10-qubit shape, which only callers who name it get, keeps
+// rot_loop: the tests of the built code look for an instance of it here.  The
+// lean loop would be 1 to 5 % faster in it (500-rotation sequences, sorted and
+// qDRIFT, rot_loop / lean: 16 qubits complex64 202 / 191 and 273 / 266 us, 24
+// qubits 2240 / 2211 and 3484 / 3460, 22 qubits complex128 1044 / 1023 and 1951 /
+// 1940).
 template <int B>
 struct TileLoop {
     static constexpr RotLoop value = B == 10 ? kRotLoop : kRotLeanTile;
